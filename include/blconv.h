@@ -107,7 +107,7 @@ typedef struct {
  * bfloat16 pair, real part in the low 16 bits, imaginary part in the high 16
  * bits: half the workspace those saved maps take in fp32.  Every channel
  * contraction multiplies the stored values exactly and accumulates in fp32
- * (the tiled path on the bf16 matrix cores); its outputs, the transforms'
+ * (on the matrix cores, or the vector ALUs where a size is at most 8); its outputs, the transforms'
  * arithmetic and the layer's inputs and outputs stay fp32.  Expected deviation
  * from the fp32 path: about 2e-3 relative (8 significant bits per operand). */
 #define BL_DESC_BF16_SPECTRA 0x1u
@@ -192,10 +192,9 @@ bl_status_t bl_conv_backward_weight(bl_conv_plan_t plan, const float* x, const f
 /* Both gradients of one layer (Sec. 3.2.3): dx as bl_conv_backward_input and
  * dw as bl_conv_backward_weight compute them, from one output-gradient
  * spectrum DY.  The two per-bin contractions run as one launch when both use
- * the tiled kernel with one tile shape, no k split and sums of the same length
- * (C_out = N: their tiles then share the GPU), else one after the other;
- * either way every output element is the same sum, in the same order, as in
- * the separate calls with the same tile shape.  Writes DY, W and X to ws; flags: any of BL_REUSE_X, BL_REUSE_W,
+ * the tiled kernel and C_out is even, else one after the other; every output
+ * element is the same sum as in the separate calls, cut into k ranges at other
+ * places where few tiles would leave the GPU idle.  Writes DY, W and X to ws; flags: any of BL_REUSE_X, BL_REUSE_W,
  * BL_REUSE_DY (the tensor may then be NULL).  dx, dw and ws may not be NULL;
  * errors as the other compute calls. */
 bl_status_t bl_conv_backward(bl_conv_plan_t plan, const float* dy, const float* w, const float* x, float* dx,

@@ -188,13 +188,13 @@ extern "C" bl_status_t bl_conv_backward(bl_conv_plan_t p, const float* dy, const
   if (!(flags & BL_REUSE_W)) BL_TRY(launch_spec_filt(p, w, Wf, s));
   if (!(flags & BL_REUSE_X))
     BL_TRY(launch_spec_fwd(p, x, X, (long)p->N * p->Cin, p->Hi, p->Wi, p->pt, p->pl, s));
-  // the paired launch writes a pass that it splits along k as partial spectra
-  // (contraction-partials area), which the inverse transform adds
+  // the paired launch writes a grad-input pass that it splits along k as
+  // partial spectra (contraction-partials area), which the inverse transform adds
   float2* CP = ws_at(ws, p->off_CPart);
-  int s1 = p->bp_s1, s2 = p->bp_s2;
-  const bl_status_t st = launch_contract_bwd_pair(p, DY, Wf, s1 > 1 ? CP : T, X, s2 > 1 ? CP : DW, s);
+  int s1 = p->bp_s1;
+  const bl_status_t st = launch_contract_bwd_pair(p, DY, Wf, s1 > 1 ? CP : T, X, DW, s);
   if (st == BL_ERR_UNSUPPORTED) {
-    s1 = s2 = 1;
+    s1 = 1;
     BL_TRY(launch_contract(p, Contract::GradInput, DY, Wf, T, CP, s));
     BL_TRY(launch_contract(p, Contract::GradWeight, X, DY, DW, CP, s));
   } else if (st != BL_OK) {
@@ -206,11 +206,11 @@ extern "C" bl_status_t bl_conv_backward(bl_conv_plan_t p, const float* dy, const
     // both inverses in one launch where the 2-D fast path and the sliced
     // weight-gradient path allow it
     const bl_status_t si = launch_fft2_inv_wgrad(p, s1 > 1 ? CP : T, dx, P, p->Hi, p->Wi, p->pt, p->pl, s1,
-                                                 (size_t)p->kept * P, s2 > 1 ? CP : DW, dw, part, s2, s);
+                                                 (size_t)p->kept * P, DW, dw, part, s);
     if (si != BL_ERR_UNSUPPORTED) return si;
   }
   BL_TRY(launch_spec_inv(p, s1 > 1 ? CP : T, dx, P, p->Hi, p->Wi, p->pt, p->pl, s, s1, T));
-  return launch_wgrad_idft(p, s2 > 1 ? CP : DW, dw, part, s, s2, DW);
+  return launch_wgrad_idft(p, DW, dw, part, s);
 }
 
 // ---------------------------------------------------------------------------

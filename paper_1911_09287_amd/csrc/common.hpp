@@ -112,13 +112,8 @@ bl_status_t launch_spec_filt(const bl_conv_plan_s* p, const float* w, void* out,
 // (only 3 x 3 filters are compiled for it).
 bl_status_t launch_fft2_fwd_filt(const bl_conv_plan_s* p, const float* in, void* out, long P, int Hin, int Win,
                                  int oi, int oj, const float* w, void* wout, hipStream_t s);
-// DW[b][c][f] -> dw [F][C][Kh][Kw]; `part` holds wg_chunks x Kh Kw x C F floats
-// (times bp_s2 when the plan pairs the backward contractions).  With nsplit > 1
-// DW is the sum of nsplit partial spectra kept * C * F complex values apart
-// (their bin slices summed with the others on the sliced path, else first
-// summed into tmp, which then holds the spectrum).
-bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* dw, float* part, hipStream_t s,
-                              int nsplit = 1, float2* tmp = nullptr);
+// DW[b][c][f] -> dw [F][C][Kh][Kw]; `part` holds wg_chunks x Kh Kw x C F floats.
+bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* dw, float* part, hipStream_t s);
 
 // Operands A and Bm are stored spectra (complex64 or bfloat16 pairs); the
 // output O and the split-k partials are complex64.
@@ -130,10 +125,10 @@ bool contract_is_thin(const bl_conv_plan_s* p, Contract which);
 bl_status_t launch_contract_thin(const bl_conv_plan_s* p, Contract which, const void* A, const void* Bm,
                                  float2* O, hipStream_t s);
 // Grad-input (DX = DY W) and grad-weight (DW = X^T conj(DY)) contractions in
-// one launch where the plan pairs them (bp_s1, bp_s2 >= 1): a pass split
-// s > 1 ways along k writes s partial spectra, kept * M * N complex values
-// apart, to DX or DW, for the inverse transform to add; BL_ERR_UNSUPPORTED
-// (nothing enqueued) otherwise.
+// one launch; grad-input split bp_s1 > 1 ways along k writes that many partial
+// spectra, kept * N * C_in complex values apart, to DX, for the inverse
+// transform to add.  BL_ERR_UNSUPPORTED (nothing enqueued) where one of them
+// takes another kernel.
 bl_status_t launch_contract_bwd_pair(const bl_conv_plan_s* p, const void* DY, const void* W, float2* DX,
                                      const void* X, float2* DW, hipStream_t s);
 // out[i] = sum over s < splits of part[s n + i] in order s = 0, 1, ... (n even).
@@ -172,11 +167,11 @@ bl_status_t launch_fft2_fwd(const bl_conv_plan_s* p, const float* in, void* out,
 bl_status_t launch_fft2_inv(const bl_conv_plan_s* p, const float2* in, float* out, long P, int OH, int OW, int ci,
                             int cj, hipStream_t s, int nsplit = 1, size_t pstride = 0);
 // The input-gradient inverse (as launch_fft2_inv) and the weight-gradient
-// inverse DFT (as launch_wgrad_idft on its sliced path, wnsplit partial
-// spectra of DW) in one launch, then the slice sum; 3 x 3 filters;
+// inverse DFT (as launch_wgrad_idft on its sliced or wide path) in one launch,
+// then the slice sum; 3 x 3 filters;
 // BL_ERR_UNSUPPORTED (nothing enqueued) where either has no such path.
 bl_status_t launch_fft2_inv_wgrad(const bl_conv_plan_s* p, const float2* in, float* out, long P, int OH, int OW,
                                   int ci, int cj, int nsplit, size_t pstride, const float2* DW, float* dw, float* part,
-                                  int wnsplit, hipStream_t s);
+                                  hipStream_t s);
 
 }  // namespace blc

@@ -224,7 +224,7 @@ __global__ __launch_bounds__(kThreads) void k_wgrad_reduce(const float* __restri
   const bool live = e < Q * g.T;
   const size_t stride = (size_t)g.T * Q;
   const float* src = part + (live ? e : 0);
-  const int slices = g.chunks * max(1, g.nsplit);
+  const int slices = g.chunks;
   float acc = 0.f;
   for (int k0 = j; k0 < slices; k0 += 32) {
     float v[8];
@@ -588,27 +588,22 @@ bl_status_t wgrad_table(const bl_conv_plan_s* p, const float2** Et) {
   return plan_table(p, key, [&](std::vector<float2>& h) { host_wgrad_weights(p, h); }, Et);
 }
 
-bool wgrad_sliced_setup(const bl_conv_plan_s* p, int nsplit, WgradGeom& g, long* xblocks, int* slices, size_t* lds,
+bool wgrad_sliced_setup(const bl_conv_plan_s* p, WgradGeom& g, long* xblocks, int* slices, size_t* lds,
                         int* tc, const float2** Et) {
   g = WgradGeom{p->Cout, p->Cin, p->Kh, p->Kw, p->Kh * p->Kw, p->Lh, p->Lw, p->r_h, p->R, p->V, 0, 0,
-                (p->Cout + 15) / 16, 1, 0};
+                (p->Cout + 15) / 16};
   if (g.T > 64 || p->wg_groups > 0 || wgrad_wide(p)) return false;
   const long Q = (long)p->Cin * p->Cout;
-  if (nsplit > 1) {
-    if (p->wg_chunks <= 1 || nsplit > std::max(1, p->bp_s2)) return false;  // partial-sum area sized for these
-    g.nsplit = nsplit;
-    g.pstride = (unsigned long long)p->kept * Q;
-  }
-  g.chunks = p->wg_chunks;  // the workspace holds partial sums for this many slices (per partial spectrum)
+  g.chunks = p->wg_chunks;  // the workspace holds partial sums for this many slices
   g.bins_per_chunk = p->wg_bins;
-  if ((long)g.chunks * g.nsplit > 65535) return false;
+  if (g.chunks > 65535) return false;
   const int tmax = g.T <= 9 ? g.T : g.T <= 16 ? 16 : g.T <= 32 ? 32 : 64;  // as instantiated
   *lds = (size_t)g.bins_per_chunk * tmax * sizeof(float2);
   if ((long)*lds > kWgradSliceLds) return false;
   const int TC = chan_tile(g.T, p->Cout), TF = kThreads / TC;
   *tc = TC;
   *xblocks = TC == 1 ? (Q + kThreads - 1) / kThreads : (long)((p->Cin + TC - 1) / TC) * ((p->Cout + TF - 1) / TF);
-  *slices = g.chunks * g.nsplit;
+  *slices = g.chunks;
   return wgrad_table(p, Et) == BL_OK;
 }
 
@@ -616,33 +611,19 @@ bl_status_t launch_wgrad_reduce(const bl_conv_plan_s* p, const float* part, floa
                                 hipStream_t s) {
   const long Q = (long)p->Cin * p->Cout;
   const long rblocks = (4 * Q * g.T + kThreads - 1) / kThreads;  // four lanes per value
-  return timed_launch("wgrad_reduce", (double)Q * g.T * 4 * (g.chunks * g.nsplit + 1), 0.0, s,
+  return timed_launch("wgrad_reduce", (double)Q * g.T * 4 * (g.chunks + 1), 0.0, s,
                       [&](hipEvent_t e0, hipEvent_t e1) {
     hipExtLaunchKernelGGL(k_wgrad_reduce, dim3((unsigned)rblocks), dim3(kThreads), 0, s, e0, e1, 0, part, dw, g);
   });
 }
 
-bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* dw, float* part, hipStream_t s,
-                              int nsplit, float2* tmp) {
+bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* dw, float* part, hipStream_t s) {
   WgradGeom g{p->Cout, p->Cin, p->Kh, p->Kw, p->Kh * p->Kw, p->Lh, p->Lw, p->r_h, p->R, p->V, 0, 0,
-              (p->Cout + 15) / 16, 1, 0};
+              (p->Cout + 15) / 16};
   const long Q = (long)p->Cin * p->Cout;
   const int B = (int)p->kept;
   const int tmax_w = g.T <= 9 ? g.T : 16;
   const bool wide = wgrad_wide(p);
-  if (nsplit > 1) {
-    // partial spectra: more slices of the sliced path (whose partial-sum area
-    // the plan sized for them), else summed into tmp first
-    if (p->wg_groups == 0 && !wide && p->wg_chunks > 1 && nsplit <= std::max(1, p->bp_s2)) {
-      g.nsplit = nsplit;
-      g.pstride = (unsigned long long)B * Q;
-    } else {
-      if (!tmp) return BL_ERR_INVALID_ARG;
-      const bl_status_t st = launch_split_reduce(DW, tmp, (unsigned long long)B * Q, nsplit, s);
-      if (st != BL_OK) return st;
-      DW = tmp;
-    }
-  }
   // one pass over all bins when there are at least 256 blocks of 64 pairs,
   // or few bins (at most 256: a sixteenth per wave), and taps and table fit
   // (rows of at most 256 output channels: wider rows write dw better from the
@@ -704,16 +685,16 @@ bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* 
     }
 #undef BL_WIDE
   }
-  g.chunks = p->wg_chunks;  // the workspace holds partial sums for this many slices (per partial spectrum)
+  g.chunks = p->wg_chunks;  // the workspace holds partial sums for this many slices
   g.bins_per_chunk = p->wg_bins;
-  if ((long)g.chunks * g.nsplit > 65535) return BL_ERR_UNSUPPORTED;
+  if (g.chunks > 65535) return BL_ERR_UNSUPPORTED;
   const int tmax = g.T <= 9 ? g.T : g.T <= 16 ? 16 : g.T <= 32 ? 32 : 64;  // as instantiated below
   const size_t lds = (size_t)g.bins_per_chunk * tmax * sizeof(float2);
   if ((long)lds > kWgradSliceLds) return BL_ERR_UNSUPPORTED;
   const int TC = chan_tile(g.T, p->Cout), TF = kThreads / TC;
   const long xblocks = TC == 1 ? (Q + kThreads - 1) / kThreads : (long)((p->Cin + TC - 1) / TC) * ((p->Cout + TF - 1) / TF);
-  dim3 grid((unsigned)xblocks, (unsigned)(g.chunks * g.nsplit));
-  const double bytes = (double)Q * B * 8 * g.nsplit + (double)Q * g.T * 4;
+  dim3 grid((unsigned)xblocks, (unsigned)g.chunks);
+  const double bytes = (double)Q * B * 8 + (double)Q * g.T * 4;
   bl_status_t st;
   auto go = [&](auto kern) {
     return timed_launch("wgrad_idft", bytes, 0.0, s, [&](hipEvent_t e0, hipEvent_t e1) {
@@ -731,7 +712,7 @@ bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* 
       else if (g.T <= 32) st = go(k_wgrad_idft<32, 1>);
       else st = go(k_wgrad_idft<64, 1>);
   }
-  if (st != BL_OK || g.chunks * g.nsplit == 1) return st;
+  if (st != BL_OK || g.chunks == 1) return st;
   return launch_wgrad_reduce(p, part, dw, g, s);
 }
 

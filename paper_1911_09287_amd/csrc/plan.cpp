@@ -114,52 +114,44 @@ extern "C" bl_status_t bl_conv_plan_create(bl_conv_plan_t* out, const bl_conv_de
   p->off_T = o;  o = align_up(o + B * p->N * (size_t)std::max(p->Cin, p->Cout) * cb, 256);
   p->off_DW = o; o = align_up(o + B * p->Cin * p->Cout * cb, 256);
   // contraction tiling of the three passes, and the paired backward launch:
-  // one tile shape and no k split of their own; the pass with more k stages is
-  // split (2 to 4 ways) to the other's length
+  // one tile shape, the larger of the two passes' (64 x 64 measured best on
+  // every workload layer: the pair runs 2 to 6 us faster than its two passes).
+  // Its long tiles start first, so unequal sums need no split while the CUs
+  // have short tiles to fill in behind them; where the CUs' average load (in
+  // stages of 16 k) is less than 1.6 times the longest tile, grad-input is
+  // split along k in up to 4, its partial spectra added by the 2-D inverse (the
+  // 512-channel layer, 6 bins: 42.3 us unsplit, 38.5 split in 4; 15 bins: 66.7
+  // unsplit, 68.9 in 4)
   {
     const long Bk = p->kept, N = p->N, Ci = p->Cin, Co = p->Cout;
-    p->ct[0] = bl_contract_tiling(N, Co, Ci, Bk);
-    p->ct[1] = bl_contract_tiling(N, Ci, Co, Bk);
-    p->ct[2] = bl_contract_tiling(Ci, Co, N, Bk);
-    p->bp_s1 = p->bp_s2 = 0;
-    const BlContractTiling &t1 = p->ct[1], &t2 = p->ct[2];
-    // one shape for both passes: theirs if they agree, else the finest tile
-    p->bp_bm = t1.bm == t2.bm && t1.bn == t2.bn ? t1.bm : 64;
-    p->bp_bn = t1.bm == t2.bm && t1.bn == t2.bn ? t1.bn : 32;
-    if (t1.splits == 1 && t2.splits == 1) {
-      const long st1 = (Co + 15) / 16, st2 = (N + 15) / 16;  // k stages: grad-input sums C_out, grad-weight N
-      if (st1 == st2) {
-        p->bp_s1 = p->bp_s2 = 1;
-      } else if (st1 > st2 && st1 % st2 == 0 && st1 / st2 <= 4) {
-        p->bp_s1 = (int)(st1 / st2), p->bp_s2 = 1;
-      } else if (st2 > st1 && st2 % st1 == 0 && st2 / st1 <= 4) {
-        p->bp_s1 = 1, p->bp_s2 = (int)(st2 / st1);
-      }
-      // a split pays while the paired tiles run in about one or two rounds
-      // of the CUs' resident blocks (measured on the 64-channel layer: 2208
-      // tiles of 64 x 32, 5 per CU, 5 us faster; at 4896 tiles 5 us slower)
-      const int bm = p->bp_bm, bn = p->bp_bn;
-      const long tiles1 = Bk * ((N + bm - 1) / bm) * ((Ci + bn - 1) / bn);
-      const long tiles2 = Bk * ((Ci + bm - 1) / bm) * ((Co + bn - 1) / bn);
-      const int resident = bm == 64 && bn == 32 ? 5 : bm == 128 && bn == 64 ? 2 : 3;  // blocks per CU
-      if ((p->bp_s1 > 1 || p->bp_s2 > 1) && tiles1 * p->bp_s1 + tiles2 * p->bp_s2 > 2L * resident * 256)
-        p->bp_s1 = p->bp_s2 = 0;
-    }
+    p->ct[0] = bl_contract_tiling(N, Co, Ci, Bk, p->bf16);
+    p->ct[1] = bl_contract_tiling(N, Ci, Co, Bk, p->bf16);
+    p->ct[2] = bl_contract_tiling(Ci, Co, N, Bk, p->bf16);
+    p->bp_s1 = 1;
+    p->bp_bm = std::max(p->ct[1].bm, p->ct[2].bm);
+    p->bp_bn = std::max(p->ct[1].bn, p->ct[2].bn);
+    const long bm = p->bp_bm, bn = p->bp_bn, st1 = (Co + 15) / 16, st2 = (N + 15) / 16;
+    const long tiles1 = Bk * ((N + bm - 1) / bm) * ((Ci + bn - 1) / bn);
+    const long tiles2 = Bk * ((Ci + bm - 1) / bm) * ((Co + bn - 1) / bn);
+    const double load = (double)(tiles1 * st1 + tiles2 * st2) / 256.0;
+    if (p->Lh > 1)
+      while (p->bp_s1 < 4 && st1 % (2 * p->bp_s1) == 0 && st1 / p->bp_s1 >= 16 && 1.6 * st1 / p->bp_s1 > load) p->bp_s1 *= 2;
   }
-  // a forward contraction with no more tiles than CUs (run with two wave
-  // groups per tile) is split along k instead, into up to 4 ranges of at least
-  // 8 stages and at most 768 tiles in all, when the 2-D inverse can add the
-  // partial spectra as it loads them (the 512-channel layer at c = 0.5: 192
-  // tiles of 32 stages become 768 of 8)
+  // forward contractions with long sums in at most two tiles per CU are split
+  // along k where the 2-D inverse can add the partial spectra as it loads them
+  // (512 channels, contraction and inverse, unsplit against split in 2: 24 bins
+  // 47.4 and 41.5 us, 15 bins 34.0 and 30.0, 6 bins 29.4 and 19.5; with 256
+  // channels, 28 bins, 20.4 and 21.7: sums of 16 stages stay whole)
   p->fwd_split = 1;
   {
     const BlContractTiling& t0 = p->ct[0];
     const long tiles0 = (long)p->kept * ((p->N + t0.bm - 1) / t0.bm) * ((p->Cout + t0.bn - 1) / t0.bn);
     const long st0 = (p->Cin + 15) / 16;
-    if (p->Lh > 1 && t0.splits == 1 && t0.ks == 2)
-      while (p->fwd_split < 4 && st0 % (2 * p->fwd_split) == 0 && st0 / (2 * p->fwd_split) >= 8 &&
-             tiles0 * 2 * p->fwd_split <= 768)
+    if (p->Lh > 1)
+      while (p->fwd_split < 4 && st0 % (2 * p->fwd_split) == 0 && st0 / p->fwd_split >= 32 &&
+             tiles0 * p->fwd_split <= 512)
         p->fwd_split *= 2;
+    p->fwd_ks = bl_contract_groups(t0.bm, t0.bn, tiles0 * p->fwd_split, st0 / p->fwd_split, p->bf16);
   }
   // partial sums of the weight-gradient inverse DFT over bin slices: enough
   // slices for ~1024 blocks of 256 (c, f) pairs, at least 16 bins per slice,
@@ -191,8 +183,7 @@ extern "C" bl_status_t bl_conv_plan_create(bl_conv_plan_t* out, const bl_conv_de
                       (long)ng * 256 * tm * 4 <= 64 * 1024) ? ng : 0;
     }
     p->off_Part = o;
-    // (k-split partial spectra of a paired backward launch count as more slices)
-    o = align_up(o + (chunks > 1 ? (size_t)std::max(1, p->bp_s2) * chunks * Q * p->Kh * p->Kw * sizeof(float) : 0),
+    o = align_up(o + (chunks > 1 ? (size_t)chunks * Q * p->Kh * p->Kw * sizeof(float) : 0),
                  256);
   }
   // split-k partial tiles of the contraction (largest of the three passes and
@@ -205,7 +196,6 @@ extern "C" bl_status_t bl_conv_plan_create(bl_conv_plan_t* out, const bl_conv_de
       if (p->ct[i].splits > 1) need = std::max(need, (size_t)p->ct[i].splits * Bk * mn[i] * cb);
     if (p->fwd_split > 1) need = std::max(need, (size_t)p->fwd_split * Bk * mn[0] * cb);
     if (p->bp_s1 > 1) need = std::max(need, (size_t)p->bp_s1 * Bk * mn[1] * cb);
-    if (p->bp_s2 > 1) need = std::max(need, (size_t)p->bp_s2 * Bk * mn[2] * cb);
     p->off_CPart = o;
     o = align_up(o + need, 256);
   }

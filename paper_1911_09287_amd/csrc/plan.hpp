@@ -13,51 +13,38 @@
 
 #include "../../include/blconv.h"
 
-// Tiling of the per-bin contraction [M x K] . [K x N] (complex) over `bins`
-// bins: tile height bm (64 or 128 rows), tile width bn (32 or 64 complex
-// columns) and the number of k-splits.  Each candidate is priced by a model
-// of a 256-CU part: a CU runs its share of the tiles one after another on its
-// matrix cores (the busiest CU sets the time), every tile pays a fixed start
-// (operand latency before the first MFMA), and k-splits add a pass that sums
-// the partial tiles in a fixed order (deterministic results) at HBM speed.
 // Dynamic LDS of one weight-gradient slice (its inverse-DFT weights): with
 // the kernel's static LDS (at most 16 KB) a block stays within 64 KB.
 constexpr long kWgradSliceLds = 48 * 1024;
 
+// Tiling of the per-bin contraction [M x K] . [K x N] (complex) over `bins`
+// bins: tile height bm and width bn (32 or 64), the number of k-splits, whose
+// partial tiles a separate pass sums in a fixed order, and the groups of waves
+// that share a block's k range.
 struct BlContractTiling {
-  int bm, bn, splits;
-  int ks;  // groups of 4 waves per block splitting the tile's k range (fp32 tiles, 1 or 2)
+  int bm, bn, splits, ks;
 };
-inline BlContractTiling bl_contract_tiling(long M, long N, long K, long bins) {
-  // constants fitted to measured launches of the tiles on an MI355X: the
-  // matrix cores reach about 60% (1 or 4 MFMA chains per wave) or 50%
-  // (2 chains) of their rate inside a tile
-  const double kCUs = 256, kClock = 2.4e9, kStart = 0.3e-6, kHbm = 5.0e12, kPass = 4e-6;
-  BlContractTiling best{64, 64, 1, 1};
-  double best_t = 1e30;
-  const int shapes[4][2] = {{128, 64}, {64, 64}, {128, 32}, {64, 32}};
-  for (const auto& sh : shapes) {
-    const int bm = sh[0], bn = sh[1];
-    if (bm == 128 && M <= 64) continue;
-    if (bn == 64 && N <= 32) continue;
-    for (int splits = 1; splits <= 16; splits *= 2) {
-      const long kper = ((K + splits - 1) / splits + 15) / 16 * 16;
-      if (splits > 1 && kper < 64) break;
-      const long tiles = bins * ((M + bm - 1) / bm) * ((N + bn - 1) / bn) * splits;
-      const double per_cu = std::ceil(tiles / kCUs);
-      // one wave per SIMD per tile: (bm/64)(bn/32) MFMAs of 64 cycles per complex k
-      const int chains = (bm / 64) * (bn / 32);
-      const double mfma = chains * 64.0 * kper / kClock / (chains == 2 ? 0.5 : 0.6);
-      double t = per_cu * (mfma + kStart);
-      if (splits > 1) t += kPass + 8.0 * bins * M * N * (splits + 1) / kHbm;
-      if (t < best_t * 0.98) best_t = t, best = BlContractTiling{bm, bn, splits, 1};
-    }
-  }
-  // no more tiles than compute units: one wave per SIMD would run each tile,
-  // so two groups of four waves split its k range instead
-  const long tiles = bins * ((M + best.bm - 1) / best.bm) * ((N + best.bn - 1) / best.bn) * best.splits;
-  if (tiles <= (long)kCUs && best.bm == 64) best.ks = 2;
-  return best;
+// Wave groups of a tile in a launch of `tiles` tiles with complex64 operands
+// and more than one stage of 16 k: with no more tiles than compute units a
+// SIMD would run one wave, whose stages (about 0.9 us each) are a serial chain
+// (128 -> 32 channels, 45 to 84 bins: 8.9 us with one group, 7.6 with four; 256
+// channels, 224 tiles: 16.5 and 15.5).  bfloat16 stages are short and memory
+// bound: 5.4 us with one group, 5.9 with four.
+inline int bl_contract_groups(int bm, int bn, long tiles, long stages, bool bf16) {
+  return bf16 || tiles > 256 || stages < 2 ? 1 : bm == 64 && bn == 64 ? 2 : 4;
+}
+inline BlContractTiling bl_contract_tiling(long M, long N, long K, long bins, bool bf16) {
+  // 64 x 64 tiles wherever both sides pass 32 (smaller ones load more per
+  // product: 1.2 to 1.8 times the time on the workload layers), 32 where a
+  // side would be mostly padding
+  BlContractTiling t{M <= 32 ? 32 : 64, N <= 32 ? 32 : 64, 1, 1};
+  const long tiles = bins * ((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+  const long stages = (K + 15) / 16;
+  t.ks = bl_contract_groups(t.bm, t.bn, tiles, stages, bf16);
+  // a handful of tiles with long sums: the pass that adds the partial tiles
+  // costs about 4 us, a stage nearly 1 us
+  while (t.splits < 16 && tiles * t.splits <= 128 && stages / (t.ks * t.splits) >= 8) t.splits *= 2;
+  return t;
 }
 
 struct bl_conv_plan_s {
@@ -85,14 +72,13 @@ struct bl_conv_plan_s {
   int wg_groups;        // groups of 256 threads per block summing parts of a slice (1, 2 or 4)
   BlContractTiling ct[3];  // contraction tiling: forward, grad-input, grad-weight
   // paired backward contraction (one launch for grad-input and grad-weight):
-  // k-splits of the two passes (the longer split so that both have tiles of
-  // equal k length; partial sums in the contraction-partials area, added by
-  // the inverse transforms); 0 when the passes are not paired
-  int bp_s1, bp_s2;
+  // k-splits of grad-input, whose partial sums (in the contraction-partials
+  // area) the inverse transform adds
+  int bp_s1;
   int bp_bm, bp_bn;  // the paired launch's tile shape
   // forward contraction split along k into partial spectra that the 2-D
   // output inverse adds (1: not split), for launches of few tiles
-  int fwd_split;
+  int fwd_split, fwd_ks;  // (fwd_ks: wave groups per tile, as BlContractTiling::ks)
   size_t off_X, off_W, off_DY, off_T, off_DW, off_Part, off_CPart, ws_bytes;
   // small device tables (1-D chirps and filter spectra, weight-gradient
   // inverse-DFT weights), built on a plan's first call that needs them on

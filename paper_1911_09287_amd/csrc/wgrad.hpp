@@ -23,16 +23,13 @@ struct WgradGeom {
   int Lh, Lw, r_h, R, V;
   int bins_per_chunk, chunks;
   int tiles_f;  // 16-filter tiles along F (k_wgrad_tile)
-  int nsplit;   // k_wgrad_idft: partial spectra of DW (their slices are more slices; 0 or 1: one)
-  unsigned long long pstride;  // complex values between two partial spectra
 };
 
 // LDS of the transposed write (TC > 1), floats.
 template <int TMAX, int TC>
 constexpr int wgrad_res_floats() { return TC > 1 ? (kThreads / TC) * TC * TMAX : 1; }
 
-// One block of the sliced inverse DFT: channel block bx, slice by (bin chunk
-// by % chunks of partial spectrum by / chunks); `sliced`: more than one slice
+// One block of the sliced inverse DFT: channel block bx, bin slice by; `sliced`: more than one slice
 // (partial sums to `part`, added later by k_wgrad_reduce).  E: the launch's
 // dynamic LDS (bins_per_chunk x TMAX float2); res: wgrad_res_floats floats.
 template <int TMAX, int TC>
@@ -41,10 +38,8 @@ __device__ __forceinline__ void wgrad_idft_block(const float2* __restrict__ DW, 
                                                  unsigned bx, unsigned by, bool sliced, float2* E, float* res) {
   constexpr int TF = kThreads / TC;
   const int B = g.R * g.V;
-  const int sp = by / g.chunks;
-  const int b0 = (by - sp * g.chunks) * g.bins_per_chunk;
+  const int b0 = by * g.bins_per_chunk;
   const int nb = min(g.bins_per_chunk, B - b0);
-  DW += (size_t)sp * g.pstride;
   // copy this slice of the table, four loads of a thread in flight together
   const float2* Es = Et + (size_t)b0 * g.T;
   for (int e0 = threadIdx.x; e0 < nb * TMAX; e0 += 4 * kThreads) {
@@ -117,13 +112,12 @@ __device__ __forceinline__ void wgrad_idft_block(const float2* __restrict__ DW, 
 }
 
 // Wide layers (many (c, f) pairs): one block per 64 consecutive pairs and all
-// bins (of one spectrum, or with PARTS the sum of g.nsplit partial spectra
-// g.pstride apart), its waves each reducing a share of the bins; the shares are
+// bins, its waves each reducing a share of the bins; the shares are
 // added in a fixed order through LDS and written straight to dw, so no
 // partial sums leave the block.  E comes from a table built once per plan.
 // E: the launch's dynamic LDS ([kept][TMAX] float2, zero beyond T: the bin loop
 // has no branches); red: NW * 64 * TMAX floats.  Block bx of 64 * NW threads.
-template <int TMAX, int NW, bool PARTS = false>
+template <int TMAX, int NW>
 __device__ __forceinline__ void wgrad_wide_block(const float2* __restrict__ DW, const float2* __restrict__ Et,
                                                  float* __restrict__ dw, const WgradGeom& g, unsigned bx, float2* E,
                                                  float* red) {
@@ -142,22 +136,11 @@ __device__ __forceinline__ void wgrad_wide_block(const float2* __restrict__ DW, 
 #pragma unroll
   for (int t = 0; t < TMAX; ++t) acc[t] = 0.f;
   const float2* src = DW + (valid ? q : 0u);
-  // 8 bins' loads in flight at a time (indices clamped, surplus values zeroed);
-  // with partial spectra (nsplit > 1) each bin is their sum, taken in order
+  // 8 bins' loads in flight at a time (indices clamped, surplus values zeroed)
   for (int bb = bb0; bb < bb1; bb += 8) {
     float2 d[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) d[j] = src[(size_t)min(bb + j, bb1 - 1) * Q];
-    if constexpr (PARTS) {
-      for (int sp = 1; sp < g.nsplit; ++sp) {
-        const float2* ps = src + (size_t)sp * g.pstride;
-        float2 e[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) e[j] = ps[(size_t)min(bb + j, bb1 - 1) * Q];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) d[j] = make_float2(d[j].x + e[j].x, d[j].y + e[j].y);
-      }
-    }
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
       const bool in = bb + j < bb1;
@@ -188,12 +171,12 @@ bool wgrad_wide(const bl_conv_plan_s* p);
 // Its E table (E[bin][t], built once per plan).
 bl_status_t wgrad_table(const bl_conv_plan_s* p, const float2** Et);
 
-// Geometry of the sliced path for a plan (nsplit partial spectra of DW): the
-// channel blocks, slices (nsplit x bin chunks), dynamic LDS bytes, channel
+// Geometry of the sliced path for a plan: the channel blocks, bin slices,
+// dynamic LDS bytes, channel
 // tile and the E table; false when the plan's inverse DFT takes another path
 // (channel tiles over all bins, or wide one-pass blocks) or the slices do not
 // fit.
-bool wgrad_sliced_setup(const bl_conv_plan_s* p, int nsplit, WgradGeom& g, long* xblocks, int* slices, size_t* lds,
+bool wgrad_sliced_setup(const bl_conv_plan_s* p, WgradGeom& g, long* xblocks, int* slices, size_t* lds,
                         int* tc, const float2** Et);
 // Sum of a sliced launch's partial sums into dw (when it had more than one slice).
 bl_status_t launch_wgrad_reduce(const bl_conv_plan_s* p, const float* part, float* dw, const WgradGeom& g,
