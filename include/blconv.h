@@ -46,14 +46,18 @@
  *
  * Ownership: the caller owns every device buffer (x, w, y, dy, dx, dw and the
  * workspace ws).  Creating and querying a plan makes no HIP call.  The plan
- * also owns small device tables, built in double precision on the host: those
- * of its 1-D transforms (chirps, the chirp filter's spectrum and twiddles:
- * under 100 KB), the roots of unity of the filter DFT (8 (L_h + L_w) bytes)
- * and the inverse-DFT weights of the weight gradient (8 K^2 bytes per kept
- * bin, K^2 -> K in 1-D).  The first compute call of
- * the plan that needs a table on a device uploads it there; that call
- * allocates and copies synchronously, so make each kind of call once outside
- * stream capture before capturing it.  Every other compute call allocates nothing,
+ * also owns device tables, built in double precision on the host or from
+ * double-precision roots on the device: the operands of transforms that run as
+ * matrix products (2-D grids without their own FFT kernels: 12 bytes per kept
+ * column and input column, and per kept row and input row; series and small
+ * planes: 12 bytes per kept bin and sample of a plane, at most 64 MiB a
+ * table), those of the chirp-z 1-D transforms (under 100 KB), the roots of
+ * unity of the filter DFT (8 (L_h + L_w) bytes) and the inverse-DFT weights of
+ * the weight gradient (8 to 12 bytes per kept bin and filter tap).  The first
+ * compute call of the plan that needs a table on a device builds it there; that call
+ * allocates and synchronises, so make each kind of call once outside
+ * stream capture before capturing it.  Where memory for a product's table is
+ * short, the transform takes a path without it.  Every other compute call allocates nothing,
  * makes no host synchronisation and enqueues its kernels on `stream` (a
  * hipStream_t, passed as void*; NULL = the default stream).
  * bl_conv_plan_destroy frees the tables (no kernel of the plan may still be
@@ -207,8 +211,8 @@ bl_status_t bl_conv_backward(bl_conv_plan_t plan, const float* dy, const float* 
  * output spectra (and the contraction's partial sums) in one static device
  * array of 64 MiB that the library holds on each GPU it runs on until the
  * process ends, instead of a caller workspace; it calls no hipMalloc or
- * hipFree and uses no plan table (the chirp-z 1-D transforms are replaced by
- * the direct DFT, and the filter transform computes its roots of unity), so
+ * hipFree and uses no plan table (matrix-product and chirp-z transforms are
+ * replaced by the direct DFT, and the filter transform computes its roots of unity), so
  * even a plan's first call allocates nothing.  The array is located once per
  * device (hipGetSymbolAddress), on the first call on that device.
  *

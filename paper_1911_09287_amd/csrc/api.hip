@@ -35,17 +35,52 @@ hipEvent_t prof_event(int slot, int end) { return g_prof.ev[2 * slot + end]; }
 // ---------------------------------------------------------------------------
 // Stage dispatch: the fast transform for the shape when there is one, else
 // the direct pruned DFT.
+//
+// rows, K: table rows (two per kept bin forward, output samples inverse) and
+// inner size of the one-product transform; P planes.  Measured on one MI355X,
+// forward / inverse in us:
+//  - series: the product beats the chirp-z FFTs until its multiply-adds fill
+//    the chip, later where those run at 256 or 512 points, without the
+//    1024-point kernel's half-wave FFTs.  270 samples, c = 0.5: 2048 series
+//    6.8 / 5.0 against 11.8 / 11.4, 8192 series 15.4 / 12.0 against 15.6 / 14.8;
+//    512 samples, c = 0.5 (1024 points): 256 series 4.4 / 4.1 against 9.7 / 9.7,
+//    2048 series 12.0 / 11.8 against 11.0 / 10.7.  Past about 700 samples only
+//    the direct sum is left: 1000 samples, 2048 series 58 / 55 against 468 / 603.
+//  - planes on grids without FFT kernels: one product while its table is small
+//    or the planes few, else two (mdft.hip).  10 x 10, c = 0, 8192 planes 8.2 /
+//    8.5 against 10.3 / 9.9; 12 x 12 11.7 / 10.4 against 10.0 / 10.5; 14 x 14,
+//    512 planes 4.0 / 4.0 against 5.6 / 4.6, 8192 planes 18.4 / 17.0 against
+//    15.5 / 12.5.
 // ---------------------------------------------------------------------------
+namespace {
+double product_macs(long rows, long K, long P) {
+  return (double)((rows + 15) / 16 * 16) * (double)((K + 31) / 32 * 32) * (double)P;
+}
+bool series_by_product(const bl_conv_plan_s* p, long rows, long K, long P, long other) {
+  const int points = bluestein_points(p, P, (int)other);
+  return points == 0 || product_macs(rows, K, P) <= (points > 512 ? 2.2e8 : 6e8);
+}
+bool planes_by_product(long rows, long K, long P) {
+  // (its k range is one chain of steps: long ones take longer than two products
+  // however few the planes: 6 planes, 32 x 32 samples from 1326 bins 21.1 against 6.0)
+  return K <= 512 && (product_macs(rows, K, 1) <= 32768.0 || product_macs(rows, K, P) <= 4e7);
+}
+}  // namespace
+
 bl_status_t launch_spec_fwd(const bl_conv_plan_s* p, const float* in, void* out, long P, int Hin, int Win, int oi,
                             int oj, hipStream_t s) {
+  bl_status_t st = BL_ERR_UNSUPPORTED;
+  const long rows = 2 * p->kept, K = (long)Hin * Win;
   if (p->Lh == 1) {
-    bl_status_t st = launch_bluestein_fwd(p, in, out, P, Win, oj, s);
-    if (st != BL_ERR_UNSUPPORTED) return st;
+    if (series_by_product(p, rows, K, P, Win)) st = launch_pgemm_fwd(p, in, out, P, Hin, Win, oi, oj, s);
+    if (st == BL_ERR_UNSUPPORTED) st = launch_bluestein_fwd(p, in, out, P, Win, oj, s);
   } else {
-    bl_status_t st = launch_fft2_fwd(p, in, out, P, Hin, Win, oi, oj, s);
-    if (st != BL_ERR_UNSUPPORTED) return st;
+    st = launch_fft2_fwd(p, in, out, P, Hin, Win, oi, oj, s);
+    if (st == BL_ERR_UNSUPPORTED && planes_by_product(rows, K, P))
+      st = launch_pgemm_fwd(p, in, out, P, Hin, Win, oi, oj, s);
+    if (st == BL_ERR_UNSUPPORTED) st = launch_mdft_fwd(p, in, out, P, Hin, Win, oi, oj, s);
   }
-  return launch_spec_fwd_direct(p, in, out, P, Hin, Win, oi, oj, s);
+  return st != BL_ERR_UNSUPPORTED ? st : launch_spec_fwd_direct(p, in, out, P, Hin, Win, oi, oj, s);
 }
 
 bl_status_t launch_contract(const bl_conv_plan_s* p, Contract which, const void* A, const void* Bm, float2* O,
@@ -60,25 +95,28 @@ bl_status_t launch_contract(const bl_conv_plan_s* p, Contract which, const void*
 
 bl_status_t launch_spec_inv(const bl_conv_plan_s* p, const float2* in, float* out, long P, int OH, int OW, int ci,
                             int cj, hipStream_t s, int nsplit, float2* tmp) {
+  bl_status_t st = BL_ERR_UNSUPPORTED;
+  const size_t n = (size_t)p->kept * P;  // between partial spectra
+  const long rows = (long)OH * OW, K = 2 * p->kept;
+  if (p->Lh > 1) {
+    st = launch_fft2_inv(p, in, out, P, OH, OW, ci, cj, s, nsplit, n);
+    if (st == BL_ERR_UNSUPPORTED && planes_by_product(rows, K, P))
+      st = launch_pgemm_inv(p, in, out, P, OH, OW, ci, cj, s, nsplit, n);
+    if (st == BL_ERR_UNSUPPORTED) st = launch_mdft_inv(p, in, out, P, OH, OW, ci, cj, s, nsplit, n);
+    if (st != BL_ERR_UNSUPPORTED) return st;
+  }
   if (nsplit > 1) {
-    const size_t n = (size_t)p->kept * P;
-    if (p->Lh > 1) {
-      const bl_status_t st = launch_fft2_inv(p, in, out, P, OH, OW, ci, cj, s, nsplit, n);
-      if (st != BL_ERR_UNSUPPORTED) return st;
-    }
     if (!tmp) return BL_ERR_INVALID_ARG;
-    const bl_status_t st = launch_split_reduce(in, tmp, n, nsplit, s);
+    st = launch_split_reduce(in, tmp, n, nsplit, s);
     if (st != BL_OK) return st;
     in = tmp;
+    st = BL_ERR_UNSUPPORTED;
   }
   if (p->Lh == 1) {
-    bl_status_t st = launch_bluestein_inv(p, in, out, P, OW, cj, s);
-    if (st != BL_ERR_UNSUPPORTED) return st;
-  } else {
-    bl_status_t st = launch_fft2_inv(p, in, out, P, OH, OW, ci, cj, s);
-    if (st != BL_ERR_UNSUPPORTED) return st;
+    if (series_by_product(p, rows, K, P, OW)) st = launch_pgemm_inv(p, in, out, P, OH, OW, ci, cj, s);
+    if (st == BL_ERR_UNSUPPORTED) st = launch_bluestein_inv(p, in, out, P, OW, cj, s);
   }
-  return launch_spec_inv_direct(p, in, out, P, OH, OW, ci, cj, s);
+  return st != BL_ERR_UNSUPPORTED ? st : launch_spec_inv_direct(p, in, out, P, OH, OW, ci, cj, s);
 }
 
 namespace {

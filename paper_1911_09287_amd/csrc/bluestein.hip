@@ -790,41 +790,54 @@ bl_status_t launch_mode(const bl_conv_plan_s* p, BlueArgs& a, int M, const void*
   return BL_ERR_UNSUPPORTED;
 }
 
-// Chooses between one series per FFT and two (when the conjugate-symmetric
-// output or input range fits the same FFT size).
+// Points of the chirp convolution's FFT (0: outside the fast path), and
+// whether two series share one (when the conjugate-symmetric output or input
+// range fits the same FFT size).
+int plan_points(int L, int V, long P, int other, bool* pack) {
+  if (2 * L > 64 * 64) return 0;
+  if ((long)V * other < 2048) return 0;  // the direct DFT is as cheap
+  const int M1 = fft_size_for(V + other - 1);
+  const int M2 = fft_size_for(2 * V - 1 + other - 1);
+  *pack = P >= 2 && 2 * (V - 1) < L && M2 <= M1 && M2 <= 1024;
+  if (!*pack && M1 > 1024) return 0;
+  return *pack ? M2 : M1;
+}
+
 bl_status_t launch_any(const bl_conv_plan_s* p, BlueArgs& a, bool inv, int other, const void* in, void* out,
                        const char* name, double bytes, hipStream_t s) {
-  if (2 * a.L > 64 * 64) return BL_ERR_UNSUPPORTED;
-  if ((long)a.V * other < 2048) return BL_ERR_UNSUPPORTED;  // the direct DFT is as cheap
-  const int M1 = fft_size_for(a.V + other - 1);
-  const int M2 = fft_size_for(2 * a.V - 1 + other - 1);
-  const bool pack = a.P >= 2 && 2 * (a.V - 1) < a.L && M2 <= M1 && M2 <= 1024;
-  if (!pack && M1 > 1024) return BL_ERR_UNSUPPORTED;
+  bool pack = false;
+  const int M = plan_points(a.L, a.V, a.P, other, &pack);
+  if (M == 0) return BL_ERR_UNSUPPORTED;
   if (!inv) {
     a.n_in = other;
     if (pack) {
       a.n_out = 2 * a.V - 1;
       a.off_out = -(a.V - 1);
-      return p->bf16 ? launch_mode<2, unsigned>(p, a, M2, in, out, name, bytes, s)
-                     : launch_mode<2, float2>(p, a, M2, in, out, name, bytes, s);
+      return p->bf16 ? launch_mode<2, unsigned>(p, a, M, in, out, name, bytes, s)
+                     : launch_mode<2, float2>(p, a, M, in, out, name, bytes, s);
     }
     a.n_out = a.V;
     a.off_out = 0;
-    return p->bf16 ? launch_mode<0, unsigned>(p, a, M1, in, out, name, bytes, s)
-                   : launch_mode<0, float2>(p, a, M1, in, out, name, bytes, s);
+    return p->bf16 ? launch_mode<0, unsigned>(p, a, M, in, out, name, bytes, s)
+                   : launch_mode<0, float2>(p, a, M, in, out, name, bytes, s);
   }
   a.n_out = other;
   if (pack) {
     a.n_in = 2 * a.V - 1;
     a.off_in = -(a.V - 1);
-    return launch_mode<3>(p, a, M2, in, out, name, bytes, s);
+    return launch_mode<3>(p, a, M, in, out, name, bytes, s);
   }
   a.n_in = a.V;
   a.off_in = 0;
-  return launch_mode<1>(p, a, M1, in, out, name, bytes, s);
+  return launch_mode<1>(p, a, M, in, out, name, bytes, s);
 }
 
 }  // namespace
+
+int bluestein_points(const bl_conv_plan_s* p, long P, int other) {
+  bool pack;
+  return plan_points(p->Lw, p->V, P, other, &pack);
+}
 
 bl_status_t launch_bluestein_fwd(const bl_conv_plan_s* p, const float* in, void* out, long P, int Win, int oj,
                                  hipStream_t s) {

@@ -79,8 +79,11 @@ __device__ inline int kept_row_d(int r, int r_h, int Lh, int R) { return r <= r_
 // ---- plan-owned device tables (tables.hip) ----------------------------------
 // Returns the device copy, on the current device, of the table identified by
 // `key`, building it with `build` (on the host) and uploading it on first use.
+// With `expand`, the table is what that makes on the device, `expanded` float2
+// long, from the uploaded data (once, before the call returns).
 bl_status_t plan_table(const bl_conv_plan_s* p, const std::vector<long>& key,
-                       const std::function<void(std::vector<float2>&)>& build, const float2** out);
+                       const std::function<void(std::vector<float2>&)>& build, const float2** out, size_t expanded = 0,
+                       const std::function<void(const float2*, float2*)>& expand = nullptr);
 long float_key(float x);  // bit pattern of x, for keys
 // Allows kernel `kern` up to `bytes` of dynamic LDS on the current device
 // (hipFuncAttributeMaxDynamicSharedMemorySize), once per kernel and device.
@@ -155,6 +158,9 @@ bl_status_t launch_bluestein_fwd(const bl_conv_plan_s* p, const float* in, void*
 bl_status_t launch_bluestein_inv(const bl_conv_plan_s* p, const float2* in, float* out, long P, int OW, int cj,
                                  hipStream_t s);
 
+// Points of its FFT for P series of `other` samples in or out; 0: outside.
+int bluestein_points(const bl_conv_plan_s* p, long P, int other);
+
 // Fused small-map forward: x -> y in one kernel (W: the stored filter
 // spectrum; X: where the input spectrum is stored for map reuse).
 bool small_fwd_eligible(const bl_conv_plan_s* p);
@@ -165,6 +171,20 @@ bl_status_t launch_small_fwd(const bl_conv_plan_s* p, const float* x, const floa
 bl_status_t launch_fft2_fwd(const bl_conv_plan_s* p, const float* in, void* out, long P, int Hin, int Win, int oi,
                             int oj, hipStream_t s);
 bl_status_t launch_fft2_inv(const bl_conv_plan_s* p, const float2* in, float* out, long P, int OH, int OW, int ci,
+                            int cj, hipStream_t s, int nsplit = 1, size_t pstride = 0);
+// Transforms of series and small planes as one product with a root table of
+// 2 kept x samples entries (at most 64 MB, a plan table).  filters > 0: the
+// planes are the (c, f) pairs of a filter bank of that many filters, samples
+// [f][c][taps], spectrum [bin][c][f].
+bl_status_t launch_pgemm_fwd(const bl_conv_plan_s* p, const float* in, void* out, long P, int Hin, int Win, int oi,
+                             int oj, hipStream_t s, int filters = 0);
+bl_status_t launch_pgemm_inv(const bl_conv_plan_s* p, const float2* in, float* out, long P, int OH, int OW, int ci,
+                             int cj, hipStream_t s, int nsplit = 1, size_t pstride = 0, int filters = 0);
+// 2-D transforms of any grid (sides up to 128 samples, 64 kept columns) as
+// matrix products; they use plan tables.
+bl_status_t launch_mdft_fwd(const bl_conv_plan_s* p, const float* in, void* out, long P, int Hin, int Win, int oi,
+                            int oj, hipStream_t s);
+bl_status_t launch_mdft_inv(const bl_conv_plan_s* p, const float2* in, float* out, long P, int OH, int OW, int ci,
                             int cj, hipStream_t s, int nsplit = 1, size_t pstride = 0);
 // The input-gradient inverse (as launch_fft2_inv) and the weight-gradient
 // inverse DFT (as launch_wgrad_idft on its sliced or wide path) in one launch,

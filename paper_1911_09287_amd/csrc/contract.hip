@@ -38,16 +38,10 @@
 #include <type_traits>
 
 #include "common.hpp"
+#include "split.hpp"
 
 namespace blc {
 namespace {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float floatx2 __attribute__((ext_vector_type(2)));
-typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
-typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
 
 // Byte offsets inside one bin's matrices are below 2^31 (checked on the host);
 // the per-bin bases are 64-bit.
@@ -139,20 +133,6 @@ __device__ __forceinline__ void load_patch(const Operand& o, int p, int k0, int 
       d.w[e][0] = v.x, d.w[e][1] = v.y;
     }
   }
-}
-
-// Two floats as three bfloat16 pairs (first value in the low half) whose sum
-// is exact: the differences are exact, and what the third part rounds is below
-// the first's 24th bit.
-__device__ __forceinline__ unsigned pack_bf16(float a, float b) {
-  return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2){a, b}, bf16x2));
-}
-__device__ __forceinline__ void split3(float a, float b, unsigned& p1, unsigned& p2, unsigned& p3) {
-  p1 = pack_bf16(a, b);
-  a -= __uint_as_float(p1 << 16), b -= __uint_as_float(p1 & 0xFFFF0000u);
-  p2 = pack_bf16(a, b);
-  a -= __uint_as_float(p2 << 16), b -= __uint_as_float(p2 & 0xFFFF0000u);
-  p3 = pack_bf16(a, b);
 }
 
 // Splits a patch and stores it: plane (part, re/im) at dst + (2 part + im) * plane.

@@ -618,6 +618,10 @@ bl_status_t launch_wgrad_reduce(const bl_conv_plan_s* p, const float* part, floa
 }
 
 bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* dw, float* part, hipStream_t s) {
+  if (wgrad_by_product(p)) {
+    const bl_status_t st = launch_pgemm_inv(p, DW, dw, (long)p->Cin * p->Cout, p->Kh, p->Kw, 0, 0, s, 1, 0, p->Cout);
+    if (st != BL_ERR_UNSUPPORTED) return st;
+  }
   WgradGeom g{p->Cout, p->Cin, p->Kh, p->Kw, p->Kh * p->Kw, p->Lh, p->Lw, p->r_h, p->R, p->V, 0, 0,
               (p->Cout + 15) / 16};
   const long Q = (long)p->Cin * p->Cout;

@@ -673,7 +673,13 @@ bl_status_t launch_inv_wgrad_t(const bl_conv_plan_s* p, const float2* in, float*
   int slices, tc;
   size_t wlds;
   const float2* Et;
-  if (!wgrad_sliced_setup(p, wg, &wx, &slices, &wlds, &tc, &Et)) {
+  const bool sliced = wgrad_sliced_setup(p, wg, &wx, &slices, &wlds, &tc, &Et);
+  // two launches either way: the matrix product spares the slice sum's (64
+  // channels, 276 bins: 17.4 + 4.1 us here, 13.5 + 6.2 apart); with few
+  // channel pairs the slices cost the transform beside them nothing (3 x 16
+  // channels: 6.0 + 3.9 us here, 5.3 + 6.1 apart)
+  if (sliced && slices > 1 && (long)p->Cin * p->Cout >= 1024 && wgrad_by_product(p)) return BL_ERR_UNSUPPORTED;
+  if (!sliced) {
     // the wide one-pass body
     if (!wgrad_wide(p) || wgrad_table(p, &Et) != BL_OK) return BL_ERR_UNSUPPORTED;
     const long Q = (long)p->Cin * p->Cout;

@@ -42,8 +42,9 @@ inline BlContractTiling bl_contract_tiling(long M, long N, long K, long bins, bo
   const long stages = (K + 15) / 16;
   t.ks = bl_contract_groups(t.bm, t.bn, tiles, stages, bf16);
   // a handful of tiles with long sums: the pass that adds the partial tiles
-  // costs about 4 us, a stage nearly 1 us
-  while (t.splits < 16 && tiles * t.splits <= 128 && stages / (t.ks * t.splits) >= 8) t.splits *= 2;
+  // costs about 4 us, a stage nearly 1 us, one of 32 k with bfloat16 half that
+  const long rounds = bf16 ? (K + 31) / 32 / 2 : stages / t.ks;
+  while (t.splits < 16 && tiles * t.splits <= 128 && rounds / t.splits >= 16) t.splits *= 2;
   return t;
 }
 

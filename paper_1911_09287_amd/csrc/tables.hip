@@ -24,7 +24,8 @@ std::mutex g_tab_mu;
 }  // namespace
 
 bl_status_t plan_table(const bl_conv_plan_s* p, const std::vector<long>& key,
-                       const std::function<void(std::vector<float2>&)>& build, const float2** out) {
+                       const std::function<void(std::vector<float2>&)>& build, const float2** out, size_t expanded,
+                       const std::function<void(const float2*, float2*)>& expand) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return BL_ERR_HIP;
   std::lock_guard<std::mutex> lk(g_tab_mu);
@@ -38,9 +39,18 @@ bl_status_t plan_table(const bl_conv_plan_s* p, const std::vector<long>& key,
     }
   std::vector<float2> host;
   build(host);
+  // the expanded table first (16-byte aligned entries), then what was uploaded
   float2* d = nullptr;
-  if (hipMalloc(&d, host.size() * sizeof(float2)) != hipSuccess) return BL_ERR_OOM;
-  if (hipMemcpy(d, host.data(), host.size() * sizeof(float2), hipMemcpyHostToDevice) != hipSuccess) {
+  if (hipMalloc(&d, (expanded + host.size()) * sizeof(float2)) != hipSuccess) {
+    (void)hipGetLastError();
+    return BL_ERR_OOM;
+  }
+  bool ok = hipMemcpy(d + expanded, host.data(), host.size() * sizeof(float2), hipMemcpyHostToDevice) == hipSuccess;
+  if (ok && expand) {
+    expand(d + expanded, d);  // enqueues on the default stream
+    ok = hipGetLastError() == hipSuccess && hipStreamSynchronize(nullptr) == hipSuccess;
+  }
+  if (!ok) {
     (void)hipFree(d);
     return BL_ERR_HIP;
   }

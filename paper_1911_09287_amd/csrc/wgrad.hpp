@@ -166,6 +166,14 @@ __device__ __forceinline__ void wgrad_wide_block(const float2* __restrict__ DW, 
   }
 }
 
+// The inverse DFT runs as one matrix product (launch_pgemm_inv): filters of
+// more than 9 taps (64 x 64 channels, 5 x 5, 184 bins 19.0 -> 4.6 us with the
+// slice sum; 256 x 256, 7 x 7, 276 bins 208 -> 65), and small filter banks with
+// few bins (3 x 3, 64 x 64 channels, 276 bins 9.6 -> 6.2, 612 bins 11.0 -> 11.7;
+// 256 x 256, 28 bins 6.8 -> 9.0).
+inline bool wgrad_by_product(const bl_conv_plan_s* p) {
+  return p->Kh * p->Kw > 9 || ((long)p->Cin * p->Cout <= 16384 && p->kept <= 320);
+}
 // The one-pass wide path applies to a plan (see launch_wgrad_idft).
 bool wgrad_wide(const bl_conv_plan_s* p);
 // Its E table (E[bin][t], built once per plan).

@@ -52,3 +52,69 @@ def test_contraction_tiles(torch, N, ci, co, hw, bf16):
     errs = [rel(g, r) for g, r in zip(got[:3] + (dx.cpu().numpy(), dw.cpu().numpy()), ref + ref[1:])]
     say(f"[tiles] {N} {ci}->{co} @{hw} bf16={bf16}: {errs}")
     assert max(errs) <= (BF16_TOL if bf16 else FP32_TOL), errs
+
+
+@pytest.mark.parametrize("nd,N,ci,co,sp,K,c,fft,bf16", [
+    # series: one product (any length), its k-shared and its large tiles, tails of
+    # samples (n % 4 and n % 32) and of rows, a Nyquist bin kept and not
+    (1, 1, 1, 1, (24,), 3, 0.0, None, 0),
+    (1, 2, 3, 2, (37,), 8, 0.5, None, 0),
+    (1, 3, 5, 7, (271,), 5, 0.25, None, 0),
+    (1, 2, 2, 3, (1250,), 3, 0.0, None, 0),
+    (1, 20, 33, 17, (900,), 5, 0.75, None, 0),
+    (1, 2, 3, 5, (333,), 7, 0.5, 700, 1),
+    # planes: one product, two products with 1, 2 and 4 steps of 32 either way,
+    # oblong and enlarged grids, odd and even grid sides, few and many planes
+    (2, 1, 1, 2, (5, 7), 3, 0.0, None, 0),
+    (2, 3, 5, 6, (9, 12), 5, 0.5, None, 0),
+    (2, 9, 7, 10, (13, 21), 3, 0.25, None, 0),
+    (2, 4, 17, 9, (33, 28), 5, 0.0, None, 0),
+    (2, 2, 3, 4, (28, 33), 1, 0.5, None, 0),
+    (2, 2, 2, 3, (64, 63), 3, 0.0, None, 0),
+    (2, 1, 2, 1, (100, 70), 3, 0.5, None, 0),
+    (2, 1, 2, 2, (31, 90), 7, 0.75, None, 0),
+    (2, 2, 3, 3, (20, 24), 5, 0.5, (43, 50), 0),
+    (2, 5, 40, 24, (14, 14), 7, 0.0, None, 0),
+    (2, 3, 16, 12, (23, 26), 3, 0.25, None, 1),
+])
+def test_matrix_transforms(torch, nd, N, ci, co, sp, K, c, fft, bf16):
+    """Transforms and weight-gradient inverse as matrix products on grids
+    without FFT kernels, and the combined backward."""
+    lo, hi = (K - 1) // 2, K - 1 - (K - 1) // 2
+    layer = synth.Layer("mt", nd, N, ci, co, sp[0], sp[1] if nd == 2 else 1, K, (lo, hi) * nd, "blur")
+    x, w, dy = synth.random_inputs(layer, 4300 + N)
+    got = gpu_passes(torch, layer, c, x, w, dy, fft=fft, desc_flags=blconv.BL_DESC_BF16_SPECTRA if bf16 else 0)
+    plan, ws = got[3], got[4]
+    xt, wt, dyt = (torch.from_numpy(a).to(ws.device) for a in (x, w, dy))
+    dx, dw = torch.full_like(xt, float("nan")), torch.full_like(wt, float("nan"))
+    plan.backward(dyt, wt, xt, dx, dw, ws)
+    torch.cuda.synchronize()
+    ref = oracle_passes(layer, c, x, w, dy, fft, rounding=bo.round_bf16 if bf16 else None)
+    errs = [rel(g, r) for g, r in zip(got[:3] + (dx.cpu().numpy(), dw.cpu().numpy()), ref + ref[1:])]
+    say(f"[matrix] {nd}-D {N} {ci}->{co} {sp} K{K} c{c}: {errs}")
+    assert max(errs) <= (BF16_TOL if bf16 else FP32_TOL), errs
+
+
+def test_matrix_transforms_keep_planes_apart(torch):
+    """A sample of infinities spoils only itself, and unaligned inputs and
+    outputs give the same as aligned ones (the loads are 16 bytes wide)."""
+    dev = torch.device("cuda:0")
+    for spatial, pad, K in (((13, 11), (1, 1, 1, 1), 3), ((8, 5), (2, 2, 2, 2), 5), ((45,), (1, 1), 3)):
+        plan = blconv.Plan(len(spatial), 5, 6, 4, spatial, K, pad, 0.25)
+        ws = plan.workspace(dev)
+        w = torch.randn(plan.w_shape(), device=dev)
+        x = torch.randn(plan.x_shape(), device=dev)
+        y0, y1 = torch.empty(plan.y_shape(), device=dev), torch.empty(plan.y_shape(), device=dev)
+        plan.forward(x, w, y0, ws)
+        bad = x.clone()
+        bad[2] = float("inf")
+        plan.forward(bad, w, y1, ws)
+        torch.cuda.synchronize()
+        keep = [0, 1, 3, 4]
+        assert torch.equal(y0[keep], y1[keep]) and not torch.isfinite(y1[2]).any()
+        xb, yb = torch.empty(x.numel() + 1, device=dev), torch.full((y0.numel() + 1,), float("nan"), device=dev)
+        xu, yu = xb[1:].view(x.shape), yb[1:].view(y0.shape)
+        xu.copy_(x)
+        plan.forward(xu, w, yu, ws)
+        torch.cuda.synchronize()
+        assert torch.equal(yu, y0) and torch.isnan(yb[0])
