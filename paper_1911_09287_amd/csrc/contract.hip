@@ -427,7 +427,7 @@ bl_status_t launch_contract_tiled(const bl_conv_plan_s* p, Contract which, const
   const int BM = t.bm, BN = t.bn;
   const unsigned long long total = B * (unsigned long long)g.M * g.N;  // complex outputs
   // the reduction works on pairs of outputs
-  const int want = parts > 1 ? parts : total % 2 == 0 ? t.splits : 1;
+  const int want = parts > 0 ? parts : total % 2 == 0 ? t.splits : 1;
   const int splits = split_k_tiles(g, BM, BN, want, B);
   if (parts > 1 && splits != parts) return BL_ERR_UNSUPPORTED;
   float2* dst = splits > 1 ? part : O;
@@ -479,7 +479,9 @@ bl_status_t launch_contract_tiled(const bl_conv_plan_s* p, Contract which, const
 
 bl_status_t launch_contract_bwd_pair(const bl_conv_plan_s* p, const void* DY, const void* W, float2* DX,
                                      const void* X, float2* DW, hipStream_t s) {
-  if (contract_is_thin(p, Contract::GradInput) || contract_is_thin(p, Contract::GradWeight)) return BL_ERR_UNSUPPORTED;
+  // with one or two images one launch of mostly empty tiles still takes less than two on the vector ALUs
+  if (p->N > 2 && (contract_is_thin(p, Contract::GradInput) || contract_is_thin(p, Contract::GradWeight)))
+    return BL_ERR_UNSUPPORTED;
   CgemmArgs g1, g2;
   bool v1, v2;
   if (!tiled_args(p, Contract::GradInput, g1, v1) || !tiled_args(p, Contract::GradWeight, g2, v2)) return BL_ERR_UNSUPPORTED;

@@ -566,7 +566,7 @@ bl_status_t launch_mdft_fwd(const bl_conv_plan_s* p, const float* in, void* out,
                             int oj, hipStream_t s) {
   MdftSetup f;
   const bl_status_t st = mdft_fwd_setup(p, P, Hin, Win, oi, oj, f);
-  if (st != BL_OK) return st == BL_ERR_OOM ? BL_ERR_UNSUPPORTED : st;  // the direct DFT needs no table
+  if (st != BL_OK) return st;
 #define X(a, b)                                                                                                  \
   if (f.ka == a && f.kb == b)                                                                                    \
     return p->bf16 ? mdft_go(k_mdft_fwd<a, b, unsigned>, "spec_fwd_2d", f.blocks, f.lds, f.bytes, f.flops, s, in, \
@@ -582,7 +582,7 @@ bl_status_t launch_mdft_inv(const bl_conv_plan_s* p, const float2* in, float* ou
                             int cj, hipStream_t s, int nsplit, size_t pstride) {
   MdftSetup f;
   const bl_status_t st = mdft_inv_setup(p, P, OH, OW, ci, cj, nsplit, pstride, f);
-  if (st != BL_OK) return st == BL_ERR_OOM ? BL_ERR_UNSUPPORTED : st;  // the direct DFT needs no table
+  if (st != BL_OK) return st;
 #define X(a, b)                                                                                                  \
   if (f.ka == a && f.kb == b)                                                                                    \
     return f.g.nsplit > 1 ? mdft_go(k_mdft_inv<a, b, true>, "spec_inv_2d", f.blocks, f.lds, f.bytes, f.flops, s, in, \

@@ -36,6 +36,11 @@ def torch():
     (64, 1024, 64, 2, 0),  # forward split along k, its partial spectra added by the inverse
     (16, 512, 512, 4, 0),  # paired backward: grad-input split along k
     (130, 24, 64, 6, 0),   # paired backward: grad-weight with the longer sums, whole
+    (2, 3, 5, 4, 0),       # tiles that are mostly padding, either direction
+    (8, 7, 6, 9, 0),       # eight rows; few columns with few rows
+    (1, 100, 104, 13, 0),  # one row: the input gradient past its bound on vector ALUs
+    (50, 20, 1, 30, 0),    # one column past its bound
+    (40, 5, 40, 6, 1),     # bfloat16 spectra: few columns (backward), few products (forward)
     (33, 66, 70, 4, 1),    # bfloat16 spectra: a partial stage of 32 k
     (40, 35, 37, 4, 1),    # bfloat16 spectra: odd k
 ])
