@@ -111,7 +111,7 @@ typedef struct {
  * bfloat16 pair, real part in the low 16 bits, imaginary part in the high 16
  * bits: half the workspace those saved maps take in fp32.  Every channel
  * contraction multiplies the stored values exactly and accumulates in fp32
- * (on the matrix cores, or the vector ALUs where a size is at most 8); its outputs, the transforms'
+ * (on the matrix cores, or the vector ALUs where a size is small); its outputs, the transforms'
  * arithmetic and the layer's inputs and outputs stay fp32.  Expected deviation
  * from the fp32 path: about 2e-3 relative (8 significant bits per operand). */
 #define BL_DESC_BF16_SPECTRA 0x1u
@@ -218,8 +218,8 @@ bl_status_t bl_conv_backward(bl_conv_plan_t plan, const float* dy, const float* 
  *
  * Limit: kept * (N * C_in + C_in * C_out) stored elements (8 bytes, 4 with
  * BL_DESC_BF16_SPECTRA) plus kept * N * C_out * 8 bytes of output spectrum
- * (plus the contraction's k-split partials where the plan's tiling splits k),
- * each rounded up to 256 bytes, must fit 64 MiB; larger plans return
+ * (each rounded up to 256 bytes; the contraction's k-split partials are used
+ * where they fit beside them) must fit 64 MiB; larger plans return
  * BL_ERR_WORKSPACE_TOO_SMALL before anything is enqueued.  Every call on a GPU
  * shares that GPU's array and leaves its spectra there: calls that overlap on
  * one GPU (other streams, other threads) race and give wrong results, so

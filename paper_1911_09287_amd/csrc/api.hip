@@ -36,34 +36,30 @@ hipEvent_t prof_event(int slot, int end) { return g_prof.ev[2 * slot + end]; }
 // Stage dispatch: the fast transform for the shape when there is one, else
 // the direct pruned DFT.
 //
-// rows, K: table rows (two per kept bin forward, output samples inverse) and
-// inner size of the one-product transform; P planes.  Measured on one MI355X,
-// forward / inverse in us:
-//  - series: the product beats the chirp-z FFTs until its multiply-adds fill
-//    the chip, later where those run at 256 or 512 points, without the
-//    1024-point kernel's half-wave FFTs.  270 samples, c = 0.5: 2048 series
-//    6.8 / 5.0 against 11.8 / 11.4, 8192 series 15.4 / 12.0 against 15.6 / 14.8;
-//    512 samples, c = 0.5 (1024 points): 256 series 4.4 / 4.1 against 9.7 / 9.7,
-//    2048 series 12.0 / 11.8 against 11.0 / 10.7.  Past about 700 samples only
-//    the direct sum is left: 1000 samples, 2048 series 58 / 55 against 468 / 603.
+// rows, K: real outputs and inputs of the one-product transform; P planes.
+// Measured on one MI355X, forward / inverse in us:
+//  - series: the product beats chirp-z FFTs of up to 512 points at any count (270
+//    samples, c = 0.5: 2048 series 5.0 / 4.7 against 11.9 / 11.6, 16384 14.6 / 16.2
+//    against 26.1 / 23.2), and until its multiply-adds fill the chip the one of 1024 (512 samples, c = 0.5: 2048 series 9.6 / 8.7
+//    against 11.0 / 10.6, 4096 14.9 / 10.7 against 12.5 / 12.7, 8192 21.3 / 18.7
+//    against 15.0 / 15.8).  Past about 700 samples only the direct sum is left:
+//    1000 samples, 2048 series 468 / 603.
 //  - planes on grids without FFT kernels: one product while its table is small
-//    or the planes few, else two (mdft.hip).  10 x 10, c = 0, 8192 planes 8.2 /
-//    8.5 against 10.3 / 9.9; 12 x 12 11.7 / 10.4 against 10.0 / 10.5; 14 x 14,
-//    512 planes 4.0 / 4.0 against 5.6 / 4.6, 8192 planes 18.4 / 17.0 against
-//    15.5 / 12.5.
+//    or the planes few, else two (mdft.hip).  10 x 10, c = 0, 8192 planes 8.0 /
+//    5.6 against 10.4 / 10.0; 14 x 14 13.5 / 10.2 against 15.3 / 12.5; 20 x 20, 512
+//    planes 6.5 / 5.8 against 6.2 / 6.0, 8192 planes 29.7 / 25.1 against 15.0 / 21.6.
 // ---------------------------------------------------------------------------
 namespace {
 double product_macs(long rows, long K, long P) {
   return (double)((rows + 15) / 16 * 16) * (double)((K + 31) / 32 * 32) * (double)P;
 }
 bool series_by_product(const bl_conv_plan_s* p, long rows, long K, long P, long other) {
-  const int points = bluestein_points(p, P, (int)other);
-  return points == 0 || product_macs(rows, K, P) <= (points > 512 ? 2.2e8 : 6e8);
+  return !bluestein_takes(p, P, (int)other) || product_macs(rows, K, P) <= 4.5e8;
 }
 bool planes_by_product(long rows, long K, long P) {
   // (its k range is one chain of steps: long ones take longer than two products
   // however few the planes: 6 planes, 32 x 32 samples from 1326 bins 21.1 against 6.0)
-  return K <= 512 && (product_macs(rows, K, 1) <= 32768.0 || product_macs(rows, K, P) <= 4e7);
+  return K <= 512 && (product_macs(rows, K, 1) <= 65536.0 || product_macs(rows, K, P) <= 8e7);
 }
 }  // namespace
 
@@ -88,7 +84,7 @@ bl_status_t launch_contract(const bl_conv_plan_s* p, Contract which, const void*
   bl_status_t st = BL_ERR_UNSUPPORTED;
   if (contract_is_thin(p, which)) st = launch_contract_thin(p, which, A, Bm, O, s);
   if (st != BL_ERR_UNSUPPORTED) return st;
-  st = launch_contract_tiled(p, which, A, Bm, O, part, s);
+  st = launch_contract_tiled(p, which, A, Bm, O, part, s, part ? 0 : 1);
   if (st != BL_ERR_UNSUPPORTED) return st;
   return launch_contract_generic(p, which, A, Bm, O, s);
 }
@@ -317,7 +313,8 @@ extern "C" bl_status_t bl_conv_forward_noalloc(bl_conv_plan_t p, const float* x,
   const size_t sb = p->bf16 ? 4 : 8, B = (size_t)p->kept;
   const size_t nX = up256(B * p->N * p->Cin * sb), nW = up256(B * p->Cin * p->Cout * sb);
   const size_t nT = up256(B * p->N * p->Cout * 8);
-  const size_t nP = p->ct[0].splits > 1 ? up256((size_t)p->ct[0].splits * B * p->N * p->Cout * 8) : 0;
+  size_t nP = p->ct[0].splits > 1 ? up256((size_t)p->ct[0].splits * B * p->N * p->Cout * 8) : 0;
+  if (nX + nW + nT + nP > ::kNoAllocBytes) nP = 0;  // no room: the sums stay whole
   if (nX + nW + nT + nP > ::kNoAllocBytes) return BL_ERR_WORKSPACE_TOO_SMALL;
   void* base = nullptr;
   BL_TRY(scratch_on_current_device(&base));
@@ -325,7 +322,7 @@ extern "C" bl_status_t bl_conv_forward_noalloc(bl_conv_plan_t p, const float* x,
   void* X = b;
   void* Wf = b + nX;
   float2* T = reinterpret_cast<float2*>(b + nX + nW);
-  float2* part = reinterpret_cast<float2*>(b + nX + nW + nT);
+  float2* part = nP ? reinterpret_cast<float2*>(b + nX + nW + nT) : nullptr;
   hipStream_t s = static_cast<hipStream_t>(stream);
   BL_TRY(launch_spec_filt(p, w, Wf, s, /*use_table=*/false));
   if (p->fused_fwd && small_fwd_eligible(p)) {

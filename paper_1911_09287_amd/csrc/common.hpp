@@ -123,7 +123,8 @@ bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* 
 enum class Contract { Forward, GradInput, GradWeight };
 bl_status_t launch_contract(const bl_conv_plan_s* p, Contract which, const void* A, const void* Bm, float2* O,
                             float2* part, hipStream_t s);
-// One of M, N, K at most 8: memory-bound, on the vector ALUs (thin.hip).
+// One or two rows, columns or products, or few columns and rows: memory-bound,
+// on the vector ALUs (thin.hip).
 bool contract_is_thin(const bl_conv_plan_s* p, Contract which);
 bl_status_t launch_contract_thin(const bl_conv_plan_s* p, Contract which, const void* A, const void* Bm,
                                  float2* O, hipStream_t s);
@@ -136,9 +137,9 @@ bl_status_t launch_contract_bwd_pair(const bl_conv_plan_s* p, const void* DY, co
                                      const void* X, float2* DW, hipStream_t s);
 // out[i] = sum over s < splits of part[s n + i] in order s = 0, 1, ... (n even).
 bl_status_t launch_split_reduce(const float2* part, float2* out, unsigned long long n, int splits, hipStream_t s);
-// Tiled, double-buffered fp32-MFMA contraction (aligned operands) and the
+// Tiled, double-buffered contraction on the bf16 matrix cores and the
 // generic one (any strides and sizes).
-// parts > 1: split k into exactly that many ranges and leave the partial
+// parts = 1: k whole, `part` unused; parts > 1: split k into exactly that many ranges and leave the partial
 // spectra in `part` (kept * M * N complex values apart) for the consumer to add.
 bl_status_t launch_contract_tiled(const bl_conv_plan_s* p, Contract which, const void* A, const void* Bm,
                                   float2* O, float2* part, hipStream_t s, int parts = 0);
@@ -158,8 +159,8 @@ bl_status_t launch_bluestein_fwd(const bl_conv_plan_s* p, const float* in, void*
 bl_status_t launch_bluestein_inv(const bl_conv_plan_s* p, const float2* in, float* out, long P, int OW, int cj,
                                  hipStream_t s);
 
-// Points of its FFT for P series of `other` samples in or out; 0: outside.
-int bluestein_points(const bl_conv_plan_s* p, long P, int other);
+// Whether its FFT takes P series of `other` samples in or out.
+bool bluestein_takes(const bl_conv_plan_s* p, long P, int other);
 
 // Fused small-map forward: x -> y in one kernel (W: the stored filter
 // spectrum; X: where the input spectrum is stored for map reuse).

@@ -64,6 +64,8 @@ def test_contraction_tiles(torch, N, ci, co, hw, bf16):
     # samples (n % 4 and n % 32) and of rows, a Nyquist bin kept and not
     (1, 1, 1, 1, (24,), 3, 0.0, None, 0),
     (1, 2, 3, 2, (37,), 8, 0.5, None, 0),
+    (1, 3, 2, 3, (3,), 3, 0.0, None, 0),
+    (1, 40, 64, 60, (401,), 5, 0.0, None, 0),
     (1, 3, 5, 7, (271,), 5, 0.25, None, 0),
     (1, 2, 2, 3, (1250,), 3, 0.0, None, 0),
     (1, 20, 33, 17, (900,), 5, 0.75, None, 0),
@@ -71,6 +73,8 @@ def test_contraction_tiles(torch, N, ci, co, hw, bf16):
     # planes: one product, two products with 1, 2 and 4 steps of 32 either way,
     # oblong and enlarged grids, odd and even grid sides, few and many planes
     (2, 1, 1, 2, (5, 7), 3, 0.0, None, 0),
+    (2, 3, 2, 2, (1, 3), 3, 0.0, None, 0),
+    (2, 2, 3, 2, (2, 2), 1, 0.0, None, 0),
     (2, 3, 5, 6, (9, 12), 5, 0.5, None, 0),
     (2, 9, 7, 10, (13, 21), 3, 0.25, None, 0),
     (2, 4, 17, 9, (33, 28), 5, 0.0, None, 0),
@@ -123,3 +127,20 @@ def test_matrix_transforms_keep_planes_apart(torch):
         plan.forward(xu, w, yu, ws)
         torch.cuda.synchronize()
         assert torch.equal(yu, y0) and torch.isnan(yb[0])
+
+
+def test_noalloc_without_room_for_partial_spectra(torch):
+    """A plan whose forward contraction splits its sums, with spectra that fill
+    the allocation-free call's array: the sums stay whole and the call runs."""
+    layer = synth.Layer("noalloc_full", 2, 16, 1024, 512, 4, 4, 3, (1, 1, 1, 1), "blur")
+    x, w, _ = synth.random_inputs(layer, 4300)
+    plan = blconv.plan_for_layer(layer, 0.25)
+    spectra = plan.kept * (layer.N * layer.C_in + layer.C_in * layer.C_out + layer.N * layer.C_out) * 8
+    assert spectra < 64 << 20 < spectra + 2 * plan.kept * layer.N * layer.C_out * 8
+    xt, wt = (torch.from_numpy(a).to("cuda:0") for a in (x, w))
+    y = torch.full(plan.y_shape(), float("nan"), device="cuda:0")
+    plan.forward_noalloc(xt, wt, y)
+    torch.cuda.synchronize()
+    err = rel(y.cpu().numpy(), bo.forward(x, w, layer.pad, 0.25))
+    say(f"[noalloc full] {err}")
+    assert err <= FP32_TOL, err
