@@ -39,6 +39,8 @@ LIBRARY_NAMES = OrderedDict([
     ("contract_reduce", r"k_split_reduce"),
     ("wgrad_idft", r"k_wgrad_wide<|k_wgrad_idft<|k_wgrad_tile<"),
     ("wgrad_reduce", r"k_wgrad_reduce"),
+    # launched under the transforms' names, or the weight gradient's inverse DFT
+    ("matrix transforms", r"k_mdft_|k_pgemm<"),
 ])
 MARKER = "spin_kernel"
 
