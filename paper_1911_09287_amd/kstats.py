@@ -31,9 +31,9 @@ LIBRARY_NAMES = OrderedDict([
     ("spec_fwd_direct", r"k_spec_fwd<"),
     ("spec_inv_direct", r"k_spec_inv\b"),
     ("spec_filt", r"k_spec_filt<"),
-    ("contract_fwd", r"k_cgemm\w*<\d+, \d+, true, true, true, (false|true)(, \d+)?>"),
-    ("contract_dgrad", r"k_cgemm\w*<\d+, \d+, true, false, false, (false|true)(, \d+)?>"),
-    ("contract_wgrad", r"k_cgemm\w*<\d+, \d+, false, true, true, (false|true)(, \d+)?>"),
+    ("contract_fwd", r"k_cgemm<\d+, \d+, true, false, true,"),
+    ("contract_dgrad", r"k_cgemm<\d+, \d+, true, true, false,"),
+    ("contract_wgrad", r"k_cgemm<\d+, \d+, false, false, true,"),
     ("contract_bwd", r"k_cgemm_bwd<"),
     ("contract (thin, any pass)", r"k_thin_"),
     ("contract_reduce", r"k_split_reduce"),
