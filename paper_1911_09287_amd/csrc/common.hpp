@@ -135,7 +135,7 @@ bl_status_t launch_contract_thin(const bl_conv_plan_s* p, Contract which, const 
 // takes another kernel.
 bl_status_t launch_contract_bwd_pair(const bl_conv_plan_s* p, const void* DY, const void* W, float2* DX,
                                      const void* X, float2* DW, hipStream_t s);
-// out[i] = sum over s < splits of part[s n + i] in order s = 0, 1, ... (n even).
+// out[i] = sum over s < splits of part[s n + i] in order s = 0, 1, ...
 bl_status_t launch_split_reduce(const float2* part, float2* out, unsigned long long n, int splits, hipStream_t s);
 // Tiled, double-buffered contraction on the bf16 matrix cores and the
 // generic one (any strides and sizes).

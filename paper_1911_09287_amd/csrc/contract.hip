@@ -354,16 +354,16 @@ __global__ __launch_bounds__(BM * BN / 16, 2) void k_cgemm_bwd(
   }
 }
 
-// out[i] = sum over k-splits of part[s][i], in split order.
-__global__ __launch_bounds__(256) void k_split_reduce(const float4* __restrict__ part, float4* __restrict__ out,
-                                                      unsigned long long n4, int splits) {
+// out[i] = sum over k-splits of part[s][i], in split order.  V: two complex
+// values, or one where the partial spectra's odd length leaves every second
+// one off a 16-byte address.
+template <typename V>
+__global__ __launch_bounds__(256) void k_split_reduce(const V* __restrict__ part, V* __restrict__ out,
+                                                      unsigned long long n, int splits) {
   const unsigned long long i = (unsigned long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n4) return;
-  float4 acc = part[i];
-  for (int s = 1; s < splits; ++s) {
-    const float4 v = part[(unsigned long long)s * n4 + i];
-    acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
-  }
+  if (i >= n) return;
+  V acc = part[i];
+  for (int s = 1; s < splits; ++s) acc += part[(unsigned long long)s * n + i];
   out[i] = acc;
 }
 
@@ -511,12 +511,14 @@ bl_status_t launch_contract_bwd_pair(const bl_conv_plan_s* p, const void* DY, co
 }
 
 bl_status_t launch_split_reduce(const float2* part, float2* out, unsigned long long n, int splits, hipStream_t s) {
-  if (n % 2 != 0) return BL_ERR_UNSUPPORTED;  // summed as pairs of complex values
-  const unsigned long long n4 = n / 2;
-  const unsigned long long blocks = (n4 + 255) / 256;
   return timed_launch("contract_reduce", 8.0 * n * (splits + 1), 0.0, s, [&](hipEvent_t e0, hipEvent_t e1) {
-    hipExtLaunchKernelGGL(k_split_reduce, dim3((unsigned)blocks), dim3(256), 0, s, e0, e1, 0,
-                          reinterpret_cast<const float4*>(part), reinterpret_cast<float4*>(out), n4, splits);
+    auto go = [&](auto kern, auto* from, auto* to, unsigned long long m) {
+      hipExtLaunchKernelGGL(kern, dim3((unsigned)((m + 255) / 256)), dim3(256), 0, s, e0, e1, 0, from, to, m, splits);
+    };
+    if (n % 2 == 0)
+      go(k_split_reduce<floatx4>, reinterpret_cast<const floatx4*>(part), reinterpret_cast<floatx4*>(out), n / 2);
+    else
+      go(k_split_reduce<floatx2>, reinterpret_cast<const floatx2*>(part), reinterpret_cast<floatx2*>(out), n);
   });
 }
 

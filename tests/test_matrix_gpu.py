@@ -59,6 +59,31 @@ def test_contraction_tiles(torch, N, ci, co, hw, bf16):
     assert max(errs) <= (BF16_TOL if bf16 else FP32_TOL), errs
 
 
+@pytest.mark.parametrize("N,ci,co,sp,c", [
+    (3, 512, 21, (127, 3), 0.0),   # 129 x 5 grid, 387 bins: forward split in 2
+    (3, 21, 512, (5, 128), 0.25),  # 7 x 130 grid, 325 bins: paired backward, grad-input split in 2
+])
+def test_odd_partial_spectra(torch, N, ci, co, sp, c):
+    """Grids whose inverse adds no partial spectra (more than 64 rows or
+    columns kept): those of an odd number of values are summed beforehand."""
+    layer = synth.Layer("odd_parts", 2, N, ci, co, *sp, 3, (1, 1, 1, 1), "blur")
+    x, w, dy = synth.random_inputs(layer, 4500 + ci)
+    got = gpu_passes(torch, layer, c, x, w, dy)
+    plan, ws = got[3], got[4]
+    assert max(plan.r_h, plan.r_w) >= 64 and plan.kept > 256 and plan.kept * N * min(ci, co) % 2
+    xt, wt, dyt = (torch.from_numpy(a).to(ws.device) for a in (x, w, dy))
+    y, dx, dw = torch.empty_like(dyt), torch.full_like(xt, float("nan")), torch.full_like(wt, float("nan"))
+    with blconv.Profile() as prof:
+        plan.forward(xt, wt, y, ws)
+        plan.backward(dyt, wt, xt, dx, dw, ws)
+        torch.cuda.synchronize()
+    assert "contract_reduce" in [r[0] for r in prof.records()]  # (or the plan splits no longer)
+    ref = oracle_passes(layer, c, x, w, dy)
+    errs = [rel(g, r) for g, r in zip(got[:3] + (dx.cpu().numpy(), dw.cpu().numpy()), ref + ref[1:])]
+    say(f"[odd parts] {ci}->{co} @{sp}: {errs}")
+    assert max(errs) <= FP32_TOL, errs
+
+
 @pytest.mark.parametrize("nd,N,ci,co,sp,K,c,fft,bf16", [
     # series: one product (any length), its k-shared and its large tiles, tails of
     # samples (n % 4 and n % 32) and of rows, a Nyquist bin kept and not
