@@ -56,7 +56,9 @@
  * the weight gradient (8 to 12 bytes per kept bin and filter tap).  The first
  * compute call of the plan that needs a table on a device builds it there; that call
  * allocates and synchronises, so make each kind of call once outside
- * stream capture before capturing it.  Where memory for a product's table is
+ * stream capture before capturing it (a captured call that finds a transform's
+ * table missing takes a slower path without it; one that finds the weight
+ * gradient's missing returns BL_ERR_UNSUPPORTED).  Where memory for a product's table is
  * short, the transform takes a path without it.  Every other compute call allocates nothing,
  * makes no host synchronisation and enqueues its kernels on `stream` (a
  * hipStream_t, passed as void*; NULL = the default stream).

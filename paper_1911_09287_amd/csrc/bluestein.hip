@@ -428,9 +428,9 @@ void host_tables_1k(const BlueGeom& a, int mode, std::vector<float2>& out) {
 }
 
 // Device copy of the tables for this geometry (built and uploaded on first use).
-bl_status_t blue_tables(const bl_conv_plan_s* p, const BlueGeom& a, int mode, const float2** out) {
+bl_status_t blue_tables(const bl_conv_plan_s* p, const BlueGeom& a, int mode, const float2** out, hipStream_t s) {
   const std::vector<long> key{1, mode, a.n_in, a.n_out, a.off_in, a.off_out, a.L, a.nyq, float_key(a.out_scale)};
-  return plan_table(p, key, [&](std::vector<float2>& host) { host_tables_1k(a, mode, host); }, out);
+  return plan_table(p, key, [&](std::vector<float2>& host) { host_tables_1k(a, mode, host); }, out, s);
 }
 
 template <int MODE, int NR, typename S>
@@ -464,7 +464,7 @@ bl_status_t launch_1k(const bl_conv_plan_s* p, const BlueGeom& a0, const void* i
   const long rows = std::max<long>({(long)a0.n_in, (long)a0.n_out, 2L * a0.V});
   if (a0.P < 1 || a0.P * rows >= 2147483647L || a0.P * rows < 0) return BL_ERR_UNSUPPORTED;
   BlueGeom a = a0;
-  const bl_status_t ts = blue_tables(p, a, MODE, &a.tab);
+  const bl_status_t ts = blue_tables(p, a, MODE, &a.tab, s);
   if (ts != BL_OK) return ts;
   if constexpr (MODE == 0 || MODE == 2) {
     const int nr = (a.n_in + 31) / 32;

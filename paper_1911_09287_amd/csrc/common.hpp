@@ -81,9 +81,10 @@ __device__ inline int kept_row_d(int r, int r_h, int Lh, int R) { return r <= r_
 // `key`, building it with `build` (on the host) and uploading it on first use.
 // With `expand`, the table is what that makes on the device, `expanded` float2
 // long, from the uploaded data (once, before the call returns).
+// BL_ERR_UNSUPPORTED: not there yet, and the caller's stream s is being captured.
 bl_status_t plan_table(const bl_conv_plan_s* p, const std::vector<long>& key,
-                       const std::function<void(std::vector<float2>&)>& build, const float2** out, size_t expanded = 0,
-                       const std::function<void(const float2*, float2*)>& expand = nullptr);
+                       const std::function<void(std::vector<float2>&)>& build, const float2** out, hipStream_t s,
+                       size_t expanded = 0, const std::function<void(const float2*, float2*)>& expand = nullptr);
 long float_key(float x);  // bit pattern of x, for keys
 // Allows kernel `kern` up to `bytes` of dynamic LDS on the current device
 // (hipFuncAttributeMaxDynamicSharedMemorySize), once per kernel and device.

@@ -524,7 +524,7 @@ void host_filt_roots(const bl_conv_plan_s* p, std::vector<float2>& out) {
 }
 
 bl_status_t filt_setup(const bl_conv_plan_s* p, bool use_table, FiltGeom& g, const float2** roots, long* blocks,
-                       size_t* lds, double* bytes) {
+                       size_t* lds, double* bytes, hipStream_t s) {
   g = FiltGeom{p->Cout, p->Cin, p->Kh, p->Kw, p->Lh, p->Lw, p->r_h, p->R, p->V, 0, 0};
   *roots = nullptr;
   bool known = false;
@@ -546,7 +546,8 @@ bl_status_t filt_setup(const bl_conv_plan_s* p, bool use_table, FiltGeom& g, con
   *bytes = (double)CF * p->Kh * p->Kw * 4 + (double)CF * B * (p->bf16 ? 4 : 8);
   if (use_table) {
     const std::vector<long> key{3, p->Lh, p->Lw};
-    return plan_table(p, key, [&](std::vector<float2>& h) { host_filt_roots(p, h); }, roots);
+    const bl_status_t st = plan_table(p, key, [&](std::vector<float2>& h) { host_filt_roots(p, h); }, roots, s);
+    return st == BL_ERR_UNSUPPORTED ? BL_OK : st;
   }
   return BL_OK;
 }
@@ -557,7 +558,7 @@ bl_status_t launch_spec_filt(const bl_conv_plan_s* p, const float* w, void* out,
   long blocks;
   size_t lds;
   double bytes;
-  const bl_status_t st = filt_setup(p, use_table, g, &roots, &blocks, &lds, &bytes);
+  const bl_status_t st = filt_setup(p, use_table, g, &roots, &blocks, &lds, &bytes, s);
   if (st != BL_OK) return st;
   const dim3 grid((unsigned)blocks);
 #define X(a, b)                                                                                             \
@@ -583,13 +584,13 @@ bool wgrad_wide(const bl_conv_plan_s* p) {
          (long)(B * tmax_w * sizeof(float2)) <= kWgradSliceLds && Q < 2147483647L;
 }
 
-bl_status_t wgrad_table(const bl_conv_plan_s* p, const float2** Et) {
+bl_status_t wgrad_table(const bl_conv_plan_s* p, const float2** Et, hipStream_t s) {
   const std::vector<long> key{2, p->Lh, p->Lw, p->r_h, p->R, p->V, p->Kh, p->Kw};
-  return plan_table(p, key, [&](std::vector<float2>& h) { host_wgrad_weights(p, h); }, Et);
+  return plan_table(p, key, [&](std::vector<float2>& h) { host_wgrad_weights(p, h); }, Et, s);
 }
 
 bool wgrad_sliced_setup(const bl_conv_plan_s* p, WgradGeom& g, long* xblocks, int* slices, size_t* lds,
-                        int* tc, const float2** Et) {
+                        int* tc, const float2** Et, hipStream_t s) {
   g = WgradGeom{p->Cout, p->Cin, p->Kh, p->Kw, p->Kh * p->Kw, p->Lh, p->Lw, p->r_h, p->R, p->V, 0, 0,
                 (p->Cout + 15) / 16};
   if (g.T > 64 || p->wg_groups > 0 || wgrad_wide(p)) return false;
@@ -604,7 +605,7 @@ bool wgrad_sliced_setup(const bl_conv_plan_s* p, WgradGeom& g, long* xblocks, in
   *tc = TC;
   *xblocks = TC == 1 ? (Q + kThreads - 1) / kThreads : (long)((p->Cin + TC - 1) / TC) * ((p->Cout + TF - 1) / TF);
   *slices = g.chunks;
-  return wgrad_table(p, Et) == BL_OK;
+  return wgrad_table(p, Et, s) == BL_OK;
 }
 
 bl_status_t launch_wgrad_reduce(const bl_conv_plan_s* p, const float* part, float* dw, const WgradGeom& g,
@@ -634,7 +635,7 @@ bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* 
   // tiled kernel below); otherwise bin slices and a fixed-order sum
   if (g.T > 64) return BL_ERR_UNSUPPORTED;
   const float2* Et = nullptr;  // E[bin][t], built once per plan
-  const bl_status_t ts = wgrad_table(p, &Et);
+  const bl_status_t ts = wgrad_table(p, &Et, s);
   if (ts != BL_OK) return ts;
   if (p->wg_groups > 0) {  // 16 x 16 channel tiles over all bins
     const int tmax = wgrad_tmax(g.T), NG = p->wg_groups;

@@ -673,7 +673,7 @@ bl_status_t launch_inv_wgrad_t(const bl_conv_plan_s* p, const float2* in, float*
   int slices, tc;
   size_t wlds;
   const float2* Et;
-  const bool sliced = wgrad_sliced_setup(p, wg, &wx, &slices, &wlds, &tc, &Et);
+  const bool sliced = wgrad_sliced_setup(p, wg, &wx, &slices, &wlds, &tc, &Et, s);
   // two launches either way: the matrix product spares the slice sum's (64
   // channels, 276 bins: 17.4 + 4.1 us here, 13.5 + 6.2 apart); with few
   // channel pairs the slices cost the transform beside them nothing (3 x 16
@@ -681,7 +681,7 @@ bl_status_t launch_inv_wgrad_t(const bl_conv_plan_s* p, const float2* in, float*
   if (sliced && slices > 1 && (long)p->Cin * p->Cout >= 1024 && wgrad_by_product(p)) return BL_ERR_UNSUPPORTED;
   if (!sliced) {
     // the wide one-pass body
-    if (!wgrad_wide(p) || wgrad_table(p, &Et) != BL_OK) return BL_ERR_UNSUPPORTED;
+    if (!wgrad_wide(p) || wgrad_table(p, &Et, s) != BL_OK) return BL_ERR_UNSUPPORTED;
     const long Q = (long)p->Cin * p->Cout;
     wg = WgradGeom{p->Cout, p->Cin, p->Kh, p->Kw, 9, p->Lh, p->Lw, p->r_h, p->R, p->V, 0, 0, 0};
     const long wblocks = (Q + 63) / 64;
@@ -744,7 +744,7 @@ bl_status_t launch_fwd_filt_t(const bl_conv_plan_s* p, const float* in, void* ou
   long fblocks;
   size_t flds;
   double fbytes;
-  st = filt_setup(p, true, fg, &roots, &fblocks, &flds, &fbytes);
+  st = filt_setup(p, true, fg, &roots, &fblocks, &flds, &fbytes, s);
   if (st != BL_OK) return st;
   if (f.blocks + fblocks >= 2147483647L) return BL_ERR_UNSUPPORTED;
   const dim3 grid((unsigned)(f.blocks + fblocks)), block(kThreads);

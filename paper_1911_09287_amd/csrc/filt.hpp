@@ -33,12 +33,13 @@ struct FiltGeom {
   X(1, 1) X(1, 2) X(1, 3) X(1, 4) X(1, 5) X(1, 6) X(1, 7) X(1, 8) \
   X(2, 2) X(3, 3) X(4, 4) X(5, 5) X(6, 6) X(7, 7) X(8, 8)
 
-// Geometry, roots-of-unity table (or null with use_table false: the blocks
-// compute the roots), block count, dynamic LDS bytes and algorithmic bytes of
-// the filter transform of a plan.  BL_ERR_UNSUPPORTED for a filter size
+// Geometry, roots-of-unity table (or null with use_table false, or where it
+// cannot be built while s is being captured: the blocks compute the roots),
+// block count, dynamic LDS bytes and algorithmic bytes of the filter transform
+// of a plan.  BL_ERR_UNSUPPORTED for a filter size
 // outside BL_FILT_CASES or a grid too large.
 bl_status_t filt_setup(const bl_conv_plan_s* p, bool use_table, FiltGeom& g, const float2** roots, long* blocks,
-                       size_t* lds, double* bytes);
+                       size_t* lds, double* bytes, hipStream_t s);
 
 // One block (id of nb) of the filter transform: a chunk of kept bins for 256
 // (c, f) pairs.  smem: at least (Lh + Lw) float2 of LDS.

@@ -459,7 +459,8 @@ double fft_flops(const bl_conv_plan_s* p, long P, int H) {
   return (double)P * (H * 2.5 * LW * std::log2(std::max(2.0, LW)) + p->V * 5.0 * LH * std::log2(std::max(2.0, LH)));
 }
 
-bl_status_t mdft_fwd_setup(const bl_conv_plan_s* p, long P, int H, int W, int oi, int oj, MdftSetup& f) {
+bl_status_t mdft_fwd_setup(const bl_conv_plan_s* p, long P, int H, int W, int oi, int oj, MdftSetup& f,
+                           hipStream_t s) {
   f.ka = steps_of(steps32(W)), f.kb = steps_of(steps32(H));
   if (!f.ka || !f.kb || (double)p->kept * P >= 2147483647.0) return BL_ERR_UNSUPPORTED;
   MdftArgs& g = f.g;
@@ -488,7 +489,7 @@ bl_status_t mdft_fwd_setup(const bl_conv_plan_s* p, long P, int H, int W, int oi
       append_operands(h, 16 * f.g.m2, f.kb, [&](int u, int i) {
         return u > p->r_h || i >= H ? 0.0 : turn((long)u * (i + oi), p->Lh, s == 1);
       });
-  }, &tab);
+  }, &tab, s);
   if (st != BL_OK) return st == BL_ERR_OOM ? BL_ERR_UNSUPPORTED : st;  // the direct DFT needs no table
   g.t1 = reinterpret_cast<const uintx4*>(tab);
   g.t2 = g.t1 + (size_t)g.n1 * f.ka * 192;
@@ -501,7 +502,7 @@ bl_status_t mdft_fwd_setup(const bl_conv_plan_s* p, long P, int H, int W, int oi
 }
 
 bl_status_t mdft_inv_setup(const bl_conv_plan_s* p, long P, int OH, int OW, int ci, int cj, int nsplit, size_t pstride,
-                           MdftSetup& f) {
+                           MdftSetup& f, hipStream_t s) {
   f.ka = steps_of(steps32(p->r_h + 1)), f.kb = steps_of(steps32(2 * p->V));
   if (!f.ka || f.ka > 2 || !f.kb || (double)p->kept * P >= 2147483647.0) return BL_ERR_UNSUPPORTED;
   MdftArgs& g = f.g;
@@ -536,7 +537,7 @@ bl_status_t mdft_inv_setup(const bl_conv_plan_s* p, long P, int OH, int OW, int 
       const double t = turn((long)v * (j + cj), p->Lw, q & 1);
       return scale * (real ? 1.0 : 2.0) * ((q & 1) ? -t : t);
     });
-  }, &tab);
+  }, &tab, s);
   if (st != BL_OK) return st == BL_ERR_OOM ? BL_ERR_UNSUPPORTED : st;  // the direct DFT needs no table
   g.t1 = reinterpret_cast<const uintx4*>(tab);
   g.t2 = g.t1 + (size_t)2 * g.n1 * f.ka * 192;
@@ -565,7 +566,7 @@ bl_status_t mdft_go(K kern, const char* name, long blocks, size_t lds, double by
 bl_status_t launch_mdft_fwd(const bl_conv_plan_s* p, const float* in, void* out, long P, int Hin, int Win, int oi,
                             int oj, hipStream_t s) {
   MdftSetup f;
-  const bl_status_t st = mdft_fwd_setup(p, P, Hin, Win, oi, oj, f);
+  const bl_status_t st = mdft_fwd_setup(p, P, Hin, Win, oi, oj, f, s);
   if (st != BL_OK) return st;
 #define X(a, b)                                                                                                  \
   if (f.ka == a && f.kb == b)                                                                                    \
@@ -581,7 +582,7 @@ bl_status_t launch_mdft_fwd(const bl_conv_plan_s* p, const float* in, void* out,
 bl_status_t launch_mdft_inv(const bl_conv_plan_s* p, const float2* in, float* out, long P, int OH, int OW, int ci,
                             int cj, hipStream_t s, int nsplit, size_t pstride) {
   MdftSetup f;
-  const bl_status_t st = mdft_inv_setup(p, P, OH, OW, ci, cj, nsplit, pstride, f);
+  const bl_status_t st = mdft_inv_setup(p, P, OH, OW, ci, cj, nsplit, pstride, f, s);
   if (st != BL_OK) return st;
 #define X(a, b)                                                                                                  \
   if (f.ka == a && f.kb == b)                                                                                    \

@@ -290,7 +290,7 @@ bool pgemm_sizes(const bl_conv_plan_s* p, long P, long n, PgemmArgs& g) {
 }
 
 template <bool INV>
-bl_status_t pgemm_table(const bl_conv_plan_s* p, int H, int W, int oi, int oj, PgemmArgs& g) {
+bl_status_t pgemm_table(const bl_conv_plan_s* p, int H, int W, int oi, int oj, PgemmArgs& g, hipStream_t s) {
   const std::vector<long> key{6, INV, p->Lh, p->Lw, p->r_h, p->V, H, W, oi, oj};
   const size_t units = (size_t)((g.rows + 15) / 16) * g.steps * 384;  // of 16 bytes
   const size_t phases = (size_t)(g.kept + 31) / 32 * 32;              // float2, after the operands
@@ -309,7 +309,7 @@ bl_status_t pgemm_table(const bl_conv_plan_s* p, int H, int W, int oi, int oj, P
             r[at++] = std::sin(a);
           }
       },
-      &tab, 2 * units + phases,
+      &tab, s, 2 * units + phases,
       [&](const float2* d, float2* expanded) {
         const double2* rh = reinterpret_cast<const double2*>(d);
         const TableGeom t{H, W, oi, oj, p->Lh, p->Lw, p->r_h, p->R, p->V, g.kept, g.rows, g.steps, (int)phases,
@@ -360,7 +360,7 @@ bl_status_t launch_pgemm_fwd(const bl_conv_plan_s* p, const float* in, void* out
   PgemmArgs g{};
   if (!pgemm_sizes<false>(p, P, n, g)) return BL_ERR_UNSUPPORTED;
   g.F = (unsigned)filters;
-  const bl_status_t st = pgemm_table<false>(p, Hin, Win, oi, oj, g);
+  const bl_status_t st = pgemm_table<false>(p, Hin, Win, oi, oj, g, s);
   if (st != BL_OK) return st == BL_ERR_OOM ? BL_ERR_UNSUPPORTED : st;
   const double bytes = (double)P * n * 4 + (double)P * p->kept * (p->bf16 ? 4 : 8);
   const double flops = filters ? 0.0 : (double)P * 2.5 * p->Lh * p->Lw * std::log2(std::max(2.0, (double)p->Lh * p->Lw));
@@ -375,7 +375,7 @@ bl_status_t launch_pgemm_inv(const bl_conv_plan_s* p, const float2* in, float* o
   if (!pgemm_sizes<true>(p, P, n, g)) return BL_ERR_UNSUPPORTED;
   g.F = (unsigned)filters;
   g.nsplit = (unsigned)std::max(1, nsplit), g.pstride = pstride;
-  const bl_status_t st = pgemm_table<true>(p, OH, OW, ci, cj, g);
+  const bl_status_t st = pgemm_table<true>(p, OH, OW, ci, cj, g, s);
   if (st != BL_OK) return st == BL_ERR_OOM ? BL_ERR_UNSUPPORTED : st;
   const double bytes = (double)P * n * 4 + (double)P * p->kept * 8 * g.nsplit;
   const double flops = filters ? 0.0 : (double)P * 2.5 * p->Lh * p->Lw * std::log2(std::max(2.0, (double)p->Lh * p->Lw));

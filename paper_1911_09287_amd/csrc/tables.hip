@@ -24,7 +24,8 @@ std::mutex g_tab_mu;
 }  // namespace
 
 bl_status_t plan_table(const bl_conv_plan_s* p, const std::vector<long>& key,
-                       const std::function<void(std::vector<float2>&)>& build, const float2** out, size_t expanded,
+                       const std::function<void(std::vector<float2>&)>& build, const float2** out, hipStream_t s,
+                       size_t expanded,
                        const std::function<void(const float2*, float2*)>& expand) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return BL_ERR_HIP;
@@ -37,6 +38,11 @@ bl_status_t plan_table(const bl_conv_plan_s* p, const std::vector<long>& key,
       *out = e.d;
       return BL_OK;
     }
+  // a stream that is being captured allows no allocation and no wait: the
+  // caller takes a path without the table, if it has one
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
+  if (capture != hipStreamCaptureStatusNone) return BL_ERR_UNSUPPORTED;
   std::vector<float2> host;
   build(host);
   // the expanded table first (16-byte aligned entries), then what was uploaded

@@ -177,7 +177,7 @@ inline bool wgrad_by_product(const bl_conv_plan_s* p) {
 // The one-pass wide path applies to a plan (see launch_wgrad_idft).
 bool wgrad_wide(const bl_conv_plan_s* p);
 // Its E table (E[bin][t], built once per plan).
-bl_status_t wgrad_table(const bl_conv_plan_s* p, const float2** Et);
+bl_status_t wgrad_table(const bl_conv_plan_s* p, const float2** Et, hipStream_t s);
 
 // Geometry of the sliced path for a plan: the channel blocks, bin slices,
 // dynamic LDS bytes, channel
@@ -185,7 +185,7 @@ bl_status_t wgrad_table(const bl_conv_plan_s* p, const float2** Et);
 // (channel tiles over all bins, or wide one-pass blocks) or the slices do not
 // fit.
 bool wgrad_sliced_setup(const bl_conv_plan_s* p, WgradGeom& g, long* xblocks, int* slices, size_t* lds,
-                        int* tc, const float2** Et);
+                        int* tc, const float2** Et, hipStream_t s);
 // Sum of a sliced launch's partial sums into dw (when it had more than one slice).
 bl_status_t launch_wgrad_reduce(const bl_conv_plan_s* p, const float* part, float* dw, const WgradGeom& g,
                                 hipStream_t s);

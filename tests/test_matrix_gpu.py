@@ -154,6 +154,45 @@ def test_matrix_transforms_keep_planes_apart(torch):
         assert torch.equal(yu, y0) and torch.isnan(yb[0])
 
 
+@pytest.mark.parametrize("nd,sp,K", [(2, (28, 21), 5), (2, (9, 9), 3), (1, (270,), 8), (1, (512,), 5), (1, (900,), 3)])
+def test_first_call_under_capture(torch, nd, sp, K):
+    """A call captured before any table of its transforms is there (a table is
+    allocated, and nothing may be during a capture) takes the paths without:
+    the input gradient after an eager forward, and a plan's very first call.
+    The direct sums' rounding grows as the root of their length: 2e-6 for 900
+    terms, each rounding 2^-24 of partial sums up to the result."""
+    lo, hi = (K - 1) // 2, K - 1 - (K - 1) // 2
+    layer = synth.Layer("cold", nd, 4, 3, 5, sp[0], sp[1] if nd == 2 else 1, K, (lo, hi) * nd, "blur")
+    dev = torch.device("cuda:0")
+    x, w, dy = synth.random_inputs(layer, 4600)
+    ref = oracle_passes(layer, 0.5, x, w, dy)
+    xt, wt, dyt = (torch.from_numpy(a).to(dev) for a in (x, w, dy))
+    y, dx = torch.empty_like(dyt), torch.empty_like(xt)
+    for warm in (True, False):
+        plan = blconv.plan_for_layer(layer, 0.5)
+        ws = plan.workspace(dev)
+        if warm:
+            plan.forward(xt, wt, y, ws)
+        torch.cuda.synchronize()
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            if warm:
+                plan.backward_input(dyt, None, dx, ws, flags=blconv.BL_REUSE_W)
+            else:
+                plan.forward(xt, wt, y, ws)
+        for _ in range(3):
+            (dx if warm else y).fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            e = rel((dx if warm else y).cpu().numpy(), ref[1 if warm else 0])
+            say(f"[cold capture] {sp} K{K} warm={warm}: {e}")
+            assert e <= 2e-6, (warm, e)
+            plan.forward(xt, wt, y, ws)  # eager, with tables
+            torch.cuda.synchronize()
+            e = rel(y.cpu().numpy(), ref[0])
+            assert e <= FP32_TOL, e
+
+
 def test_noalloc_without_room_for_partial_spectra(torch):
     """A plan whose forward contraction splits its sums, with spectra that fill
     the allocation-free call's array: the sums stay whole and the call runs."""
