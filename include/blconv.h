@@ -46,8 +46,7 @@
  *
  * Ownership: the caller owns every device buffer (x, w, y, dy, dx, dw and the
  * workspace ws).  Creating and querying a plan makes no HIP call.  The plan
- * also owns device tables, built in double precision on the host or from
- * double-precision roots on the device: the operands of transforms that run as
+ * also owns device tables, built in double precision on the host or the device: the operands of transforms that run as
  * matrix products (2-D grids without their own FFT kernels: 12 bytes per kept
  * column and input column, and per kept row and input row; series and small
  * planes: 12 bytes per kept bin and sample of a plane, at most 64 MiB a

@@ -384,45 +384,66 @@ __global__ __launch_bounds__(kThreads) void k_mdft_inv(const float2* __restrict_
   mdft_inv_block<KA, KB, PARTS>(in, out, g, blockIdx.x, gridDim.x, smf);
 }
 
-// ---- host: tables and geometry ----------------------------------------------
-unsigned short bf16_of(double x) {  // round to nearest even
-  const float f = (float)x;  // double rounding is harmless: the next part takes up the difference
-  unsigned u;
-  __builtin_memcpy(&u, &f, 4);
-  return (unsigned short)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-}
-double bf16_value(unsigned short h) {
-  const unsigned u = (unsigned)h << 16;
-  float f;
-  __builtin_memcpy(&f, &u, 4);
-  return f;
+// ---- tables and geometry ------------------------------------------------------
+struct MdftTable {
+  int H, W, oi, oj;  // samples and their place on the grid
+  int Lh, Lw, r_h, V;
+  int ka, kb;        // steps of 32 of the two products
+  int n1, n2;        // row tiles of the two operands (both of the cosine and sine operand's sets)
+  double scale;      // inverse: 1 / (Lh Lw)
+};
+
+// The root tables of the two products as MFMA operands [tile][k step][part]
+// [lane][8], in double precision before the split; one thread per (tile, step,
+// lane).  Forward: Ew, then C and S of the kept rows; inverse: C and S of the
+// output rows, then the weighted column roots.
+template <bool INV>
+__global__ __launch_bounds__(256) void k_mdft_table(unsigned short* __restrict__ out, MdftTable g) {
+  const int id = blockIdx.x * 256 + threadIdx.x, lane = id & 63, first = g.n1 * g.ka;
+  int ts = id >> 6;  // tile and step
+  if (ts >= first + g.n2 * g.kb) return;
+  out += (size_t)ts * 1536 + lane * 8;
+  const bool one = ts < first;
+  if (!one) ts -= first;
+  const int steps = one ? g.ka : g.kb, row = (ts / steps) * 16 + (lane & 15), k0 = (ts % steps) * 32 + 8 * (lane >> 4);
+  auto turn = [](int m, int L, bool sine) {  // cos or sin of 2 pi m / L
+    double c, s;
+    sincospi(2.0 * (m % L) / L, &s, &c);
+    return sine ? s : c;
+  };
+  for (int e = 0; e < 8; ++e) {
+    const int k = k0 + e;
+    double v = 0.0;
+    if (one == INV) {  // cosines and sines along the columns of the grid
+      const int half = (one ? g.n1 : g.n2) / 2 * 16;  // the sines' first row
+      const int r = row < half ? row : row - half, u = INV ? k : r, i = INV ? r : k;
+      if (u <= g.r_h && i < g.H) v = turn(u * (i + g.oi), g.Lh, row >= half);
+    } else if constexpr (!INV) {  // x[j] e^{-2 pi i w (j + oj) / Lw}
+      const int w = row >> 1;
+      if (w < g.V && k < g.W) v = (row & 1) ? -turn(w * (k + g.oj), g.Lw, true) : turn(w * (k + g.oj), g.Lw, false);
+    } else {  // h_w Re((zr + i zi) e^{+2 pi i w (j + cj) / Lw})
+      const int w = k >> 1;
+      const bool real = w == 0 || 2 * w == g.Lw;
+      if (row < g.W && w < g.V && !(real && (k & 1))) {
+        const double t = turn(w * (row + g.oj), g.Lw, k & 1);
+        v = g.scale * (real ? 1.0 : 2.0) * ((k & 1) ? -t : t);
+      }
+    }
+    split3_store(v, out + e, 512);
+  }
 }
 
-// value(row, k) as MFMA operands [tile][k step][part][lane][8], appended to out.
-template <class F>
-void append_operands(std::vector<float2>& out, int rows, int ks, F&& value) {
-  const int tiles = (rows + 15) / 16;
-  std::vector<unsigned short> h((size_t)tiles * ks * 3 * 512, 0);
-  for (int t = 0; t < tiles; ++t)
-    for (int k = 0; k < ks; ++k)
-      for (int l = 0; l < 64; ++l)
-        for (int e = 0; e < 8; ++e) {
-          const int row = t * 16 + (l & 15), kk = 32 * k + 8 * (l >> 4) + e;
-          double v = row < rows ? value(row, kk) : 0.0;
-          for (int p = 0; p < 3; ++p) {
-            const unsigned short b = bf16_of(v);
-            h[((((size_t)t * ks + k) * 3 + p) * 64 + l) * 8 + e] = b;
-            v -= bf16_value(b);
-          }
-        }
-  const size_t at = out.size();
-  out.resize(at + h.size() / 4);
-  __builtin_memcpy(out.data() + at, h.data(), h.size() * 2);
-}
-
-double turn(long m, long L, bool sine) {  // cos or sin of 2 pi m / L, m reduced exactly
-  const double a = 2.0 * 3.141592653589793238462643383279502884 * (double)(m % L) / (double)L;
-  return sine ? std::sin(a) : std::cos(a);
+template <bool INV>
+bl_status_t mdft_table(const bl_conv_plan_s* p, const MdftTable& t, const float2** tab, hipStream_t s) {
+  const std::vector<long> key{INV ? 5 : 4, p->Lh, p->Lw, p->r_h, p->V, t.H, t.W, t.oi, t.oj};
+  const int n = t.n1 * t.ka + t.n2 * t.kb;  // of 3 KB
+  return plan_table_on_device(
+      p, key, (size_t)n * 384,
+      [&](float2* d) {
+        hipLaunchKernelGGL((k_mdft_table<INV>), dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s,
+                           reinterpret_cast<unsigned short*>(d), t);
+      },
+      tab, s);
 }
 
 int steps32(int n) { return (n + 31) / 32; }
@@ -477,19 +498,9 @@ bl_status_t mdft_fwd_setup(const bl_conv_plan_s* p, long P, int H, int W, int oi
   g.magic = magic_of((unsigned)H);
   const int run = G * (p->bf16 ? 4 : 8);
   g.K = run < 64 ? (unsigned)(128 / run) : 1u;
-  const std::vector<long> key{4, p->Lh, p->Lw, p->r_h, p->V, H, W, oi, oj};
   const float2* tab;
-  const bl_status_t st = plan_table(p, key, [&](std::vector<float2>& h) {
-    append_operands(h, 2 * p->V, f.ka, [&](int n, int j) {  // x[j] e^{-2 pi i v (j + oj) / Lw}
-      if (j >= W) return 0.0;
-      const double t = turn((long)(n >> 1) * (j + oj), p->Lw, n & 1);
-      return (n & 1) ? -t : t;
-    });
-    for (int s = 0; s < 2; ++s)
-      append_operands(h, 16 * f.g.m2, f.kb, [&](int u, int i) {
-        return u > p->r_h || i >= H ? 0.0 : turn((long)u * (i + oi), p->Lh, s == 1);
-      });
-  }, &tab, s);
+  const bl_status_t st = mdft_table<false>(
+      p, MdftTable{H, W, oi, oj, p->Lh, p->Lw, p->r_h, p->V, f.ka, f.kb, g.n1, 2 * g.m2, 1.0}, &tab, s);
   if (st != BL_OK) return st == BL_ERR_OOM ? BL_ERR_UNSUPPORTED : st;  // the direct DFT needs no table
   g.t1 = reinterpret_cast<const uintx4*>(tab);
   g.t2 = g.t1 + (size_t)g.n1 * f.ka * 192;
@@ -520,24 +531,9 @@ bl_status_t mdft_inv_setup(const bl_conv_plan_s* p, long P, int OH, int OW, int 
   g.n1 = (OH + 15) / 16, g.n2 = (OW + 15) / 16;
   g.magic = magic_of((unsigned)OH);
   g.K = G * 8 < 128 ? (unsigned)(128 / (G * 8)) : 1u;
-  const std::vector<long> key{5, p->Lh, p->Lw, p->r_h, p->V, OH, OW, ci, cj};
   const float2* tab;
-  const bl_status_t st = plan_table(p, key, [&](std::vector<float2>& h) {
-    const double scale = 1.0 / ((double)p->Lh * (double)p->Lw);
-    const int nyq = p->Lw % 2 == 0 ? p->Lw / 2 : -1;
-    for (int s = 0; s < 2; ++s)
-      append_operands(h, 16 * f.g.n1, f.ka, [&](int i, int u) {
-        return i >= OH || u > p->r_h ? 0.0 : turn((long)u * (i + ci), p->Lh, s == 1);
-      });
-    append_operands(h, 16 * f.g.n2, f.kb, [&](int j, int q) {  // h_v Re((zr + i zi) e^{+2 pi i v (j + cj) / Lw})
-      const int v = q >> 1;
-      if (j >= OW || v >= p->V) return 0.0;
-      const bool real = v == 0 || v == nyq;
-      if (real && (q & 1)) return 0.0;
-      const double t = turn((long)v * (j + cj), p->Lw, q & 1);
-      return scale * (real ? 1.0 : 2.0) * ((q & 1) ? -t : t);
-    });
-  }, &tab, s);
+  const bl_status_t st = mdft_table<true>(p, MdftTable{OH, OW, ci, cj, p->Lh, p->Lw, p->r_h, p->V, f.ka, f.kb, 2 * g.n1, g.n2,
+                                                       1.0 / ((double)p->Lh * (double)p->Lw)}, &tab, s);
   if (st != BL_OK) return st == BL_ERR_OOM ? BL_ERR_UNSUPPORTED : st;  // the direct DFT needs no table
   g.t1 = reinterpret_cast<const uintx4*>(tab);
   g.t2 = g.t1 + (size_t)2 * g.n1 * f.ka * 192;

@@ -231,30 +231,30 @@ __global__ __launch_bounds__(256, 2) void k_pgemm(const void* __restrict__ in, v
 }
 
 struct TableGeom {
-  int H, W, oi, oj, Lh, Lw, r_h, R, V;
+  int H, W, Lh, Lw, r_h, R, V;
   int kept, rows, steps, phases;
+  int oi, oj;    // grid offset of the second set of phases (the first has none)
   double scale;  // inverse: 1 / (Lh Lw)
 };
 
-// Expands the roots e^{pi i m / Lh}, e^{pi i m / Lw} (double precision) into the
-// split operands and the phases; one thread per (row tile, step, lane).
+// The operands (split root tables) and, after them, the bins' phases for both
+// of the plan's offsets, in double precision; one thread per (row tile, step, lane).
 template <bool INV>
-__global__ __launch_bounds__(256) void k_pgemm_table(const double2* __restrict__ rh, const double2* __restrict__ rw,
-                                                     unsigned short* __restrict__ out, float2* __restrict__ phase,
+__global__ __launch_bounds__(256) void k_pgemm_table(unsigned short* __restrict__ out, float2* __restrict__ phase,
                                                      TableGeom g, long n) {
   const long id = (long)blockIdx.x * 256 + threadIdx.x;
   if (id >= n) return;
-  // e^{pi i (u i / Lh + w j / Lw)}, i and j of either sign
-  auto root = [&](int b, long i, long j) {
-    const long u = kept_row_d(b / g.V, g.r_h, g.Lh, g.R), w = b % g.V;
-    const long mh = u * i % (2 * g.Lh), mw = w * j % (2 * g.Lw);
-    const double2 a = rh[mh < 0 ? mh + 2 * g.Lh : mh], q = rw[mw < 0 ? mw + 2 * g.Lw : mw];
-    return make_double2(a.x * q.x - a.y * q.y, a.x * q.y + a.y * q.x);
+  // e^{pi i (u i / Lh + w j / Lw)}, i and j of either sign (sides and samples up to 4096: products of 25 bits)
+  auto root = [&](int b, int i, int j, double* re, double* im) {
+    const int u = kept_row_d(b / g.V, g.r_h, g.Lh, g.R), w = b % g.V;
+    sincospi((double)(u * i % (2 * g.Lh)) / g.Lh + (double)(w * j % (2 * g.Lw)) / g.Lw, im, re);
   };
-  if (id < g.phases) {
-    const double2 r = root((int)min(id, (long)g.kept - 1), 2 * g.oi + g.H - 1, 2 * g.oj + g.W - 1);
-    phase[id] = make_float2((float)r.x, (float)r.y);
-  }
+  double re, im;
+  if (id < g.phases)
+    for (int set = 0; set < 2; ++set) {
+      root((int)min(id, (long)g.kept - 1), (set ? 2 * g.oi : 0) + g.H - 1, (set ? 2 * g.oj : 0) + g.W - 1, &re, &im);
+      phase[set * g.phases + id] = make_float2((float)re, (float)im);
+    }
   const int lane = (int)(id & 63);
   const long ts = id >> 6;  // row tile * steps + step
   const int row = (int)(ts / g.steps) * 16 + (lane & 15), k0 = (int)(ts % g.steps) * 32 + 8 * (lane >> 4);
@@ -264,18 +264,12 @@ __global__ __launch_bounds__(256) void k_pgemm_table(const double2* __restrict__
     double v[2] = {0.0, 0.0};
     if (b < g.kept && s < pairs) {
       const int i = s / g.W, j = s - i * g.W;
-      const double2 r = root(b, 2 * i - (g.H - 1), 2 * j - (g.W - 1));
+      root(b, 2 * i - (g.H - 1), 2 * j - (g.W - 1), &re, &im);
       // (the middle sample of an odd count is its own partner)
       const double f = INV ? g.scale * (b % g.V == 0 || 2 * (b % g.V) == g.Lw ? 1.0 : 2.0) : 2 * s + 1 == g.H * g.W ? 0.5 : 1.0;
-      v[0] = f * r.x, v[1] = -f * r.y;
+      v[0] = f * re, v[1] = -f * im;
     }
-    for (int h = 0; h < 2; ++h)
-      for (int p = 0; p < 3; ++p) {
-        const unsigned f = __float_as_uint((float)v[h]);
-        const unsigned short m = (unsigned short)((f + 0x7FFFu + ((f >> 16) & 1u)) >> 16);
-        out[(((ts * 2 + h) * 3 + p) * 64 + lane) * 8 + e] = m;
-        v[h] -= (double)__uint_as_float((unsigned)m << 16);
-      }
+    for (int h = 0; h < 2; ++h) split3_store(v[h], out + ((ts * 2 + h) * 3 * 64 + lane) * 8 + e, 512);
   }
 }
 
@@ -289,37 +283,30 @@ bool pgemm_sizes(const bl_conv_plan_s* p, long P, long n, PgemmArgs& g) {
   return true;
 }
 
+// The operands depend on the samples' shape and the band, not on where the
+// samples lie on the grid: inputs and outputs of one size share them, and the
+// phases of the plan's two places (the input's, after the padding, and the
+// output's) are kept beside them.
 template <bool INV>
 bl_status_t pgemm_table(const bl_conv_plan_s* p, int H, int W, int oi, int oj, PgemmArgs& g, hipStream_t s) {
-  const std::vector<long> key{6, INV, p->Lh, p->Lw, p->r_h, p->V, H, W, oi, oj};
+  const bool place = oi != 0 || oj != 0;
+  if (place && (oi != p->pt || oj != p->pl)) return BL_ERR_UNSUPPORTED;
+  const std::vector<long> key{6, INV, p->Lh, p->Lw, p->r_h, p->V, H, W};
   const size_t units = (size_t)((g.rows + 15) / 16) * g.steps * 384;  // of 16 bytes
   const size_t phases = (size_t)(g.kept + 31) / 32 * 32;              // float2, after the operands
-  const size_t roots = 2 * ((size_t)p->Lh + p->Lw);                   // double2, after the phases
   const float2* tab;
-  const bl_status_t st = plan_table(
-      p, key,
-      [&](std::vector<float2>& h) {
-        h.assign(2 * roots, make_float2(0.f, 0.f));
-        double* r = reinterpret_cast<double*>(h.data());
-        size_t at = 0;
-        for (int L : {p->Lh, p->Lw})
-          for (int k = 0; k < 2 * L; ++k) {
-            const double a = 3.141592653589793238462643383279502884 * (double)k / (double)L;
-            r[at++] = std::cos(a);
-            r[at++] = std::sin(a);
-          }
-      },
-      &tab, s, 2 * units + phases,
-      [&](const float2* d, float2* expanded) {
-        const double2* rh = reinterpret_cast<const double2*>(d);
-        const TableGeom t{H, W, oi, oj, p->Lh, p->Lw, p->r_h, p->R, p->V, g.kept, g.rows, g.steps, (int)phases,
+  const bl_status_t st = plan_table_on_device(
+      p, key, 2 * (units + phases),
+      [&](float2* d) {
+        const TableGeom t{H, W, p->Lh, p->Lw, p->r_h, p->R, p->V, g.kept, g.rows, g.steps, (int)phases, p->pt, p->pl,
                           1.0 / ((double)p->Lh * (double)p->Lw)};
         const long n = (long)(units / 6);
-        hipLaunchKernelGGL((k_pgemm_table<INV>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, 0, rh, rh + 2 * p->Lh,
-                           reinterpret_cast<unsigned short*>(expanded), expanded + 2 * units, t, n);
-      });
+        hipLaunchKernelGGL((k_pgemm_table<INV>), dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s,
+                           reinterpret_cast<unsigned short*>(d), d + 2 * units, t, n);
+      },
+      &tab, s);
   g.tab = reinterpret_cast<const uintx4*>(tab);
-  g.phase = tab + 2 * units;
+  g.phase = tab + 2 * units + (place ? phases : 0);
   return st;
 }
 

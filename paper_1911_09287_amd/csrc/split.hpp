@@ -31,6 +31,16 @@ __device__ __forceinline__ void split3(float a, float b, unsigned& p1, unsigned&
   p3 = pack_bf16(a, b);
 }
 
+// The same of one value in double precision, for tables: parts `stride` apart.
+__device__ __forceinline__ void split3_store(double v, unsigned short* out, int stride) {
+  for (int p = 0; p < 3; ++p) {
+    const unsigned f = __float_as_uint((float)v);  // (rounded twice: the next part takes up the difference)
+    const unsigned short h = (unsigned short)((f + 0x7FFFu + ((f >> 16) & 1u)) >> 16);
+    out[p * stride] = h;
+    v -= (double)__uint_as_float((unsigned)h << 16);
+  }
+}
+
 // An operand of eight k of a row or column, split: v = p[0] + p[1] + p[2].
 struct Split8 {
   uintx4 p[3];

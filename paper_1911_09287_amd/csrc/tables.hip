@@ -1,9 +1,10 @@
 // Small device tables owned by a plan (chirps and filter spectra of the 1-D
 // transforms, roots of unity of the filter DFT, inverse-DFT weights of the
-// weight gradient).  Each is built on
-// the host in double precision and uploaded by the plan's first call that
-// needs it on a device; the plan frees them when it is destroyed.
+// weight gradient, operands of the matrix-product transforms).  Each is built
+// in double precision, on the host and uploaded or by a kernel, in the plan's
+// first call that needs it on a device; the plan frees them when it is destroyed.
 #include <cstring>
+#include <functional>
 #include <mutex>
 #include <new>
 #include <utility>
@@ -23,10 +24,12 @@ std::mutex g_tab_mu;
 
 }  // namespace
 
-bl_status_t plan_table(const bl_conv_plan_s* p, const std::vector<long>& key,
-                       const std::function<void(std::vector<float2>&)>& build, const float2** out, hipStream_t s,
-                       size_t expanded,
-                       const std::function<void(const float2*, float2*)>& expand) {
+namespace {
+
+// The table of `key` on the current device, made by `make` (which allocates
+// and fills it) where the plan has none yet.
+bl_status_t find_or_make(const bl_conv_plan_s* p, const std::vector<long>& key, hipStream_t s, const float2** out,
+                         const std::function<bl_status_t(float2**)>& make) {
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return BL_ERR_HIP;
   std::lock_guard<std::mutex> lk(g_tab_mu);
@@ -43,26 +46,47 @@ bl_status_t plan_table(const bl_conv_plan_s* p, const std::vector<long>& key,
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
   if (capture != hipStreamCaptureStatusNone) return BL_ERR_UNSUPPORTED;
-  std::vector<float2> host;
-  build(host);
-  // the expanded table first (16-byte aligned entries), then what was uploaded
   float2* d = nullptr;
-  if (hipMalloc(&d, (expanded + host.size()) * sizeof(float2)) != hipSuccess) {
-    (void)hipGetLastError();
-    return BL_ERR_OOM;
-  }
-  bool ok = hipMemcpy(d + expanded, host.data(), host.size() * sizeof(float2), hipMemcpyHostToDevice) == hipSuccess;
-  if (ok && expand) {
-    expand(d + expanded, d);  // enqueues on the default stream
-    ok = hipGetLastError() == hipSuccess && hipStreamSynchronize(nullptr) == hipSuccess;
-  }
-  if (!ok) {
-    (void)hipFree(d);
-    return BL_ERR_HIP;
+  const bl_status_t st = make(&d);
+  if (st != BL_OK) {
+    if (d) (void)hipFree(d);
+    return st;
   }
   cache->push_back(TabEntry{dev, key, d});
   *out = d;
   return BL_OK;
+}
+
+bl_status_t allocate(float2** d, size_t n) {
+  if (hipMalloc(d, n * sizeof(float2)) == hipSuccess) return BL_OK;
+  (void)hipGetLastError();
+  *d = nullptr;
+  return BL_ERR_OOM;
+}
+
+}  // namespace
+
+bl_status_t plan_table(const bl_conv_plan_s* p, const std::vector<long>& key,
+                       const std::function<void(std::vector<float2>&)>& build, const float2** out, hipStream_t s) {
+  return find_or_make(p, key, s, out, [&](float2** d) {
+    std::vector<float2> host;
+    build(host);
+    const bl_status_t st = allocate(d, host.size());
+    if (st != BL_OK) return st;
+    return hipMemcpy(*d, host.data(), host.size() * sizeof(float2), hipMemcpyHostToDevice) == hipSuccess ? BL_OK
+                                                                                                        : BL_ERR_HIP;
+  });
+}
+
+bl_status_t plan_table_on_device(const bl_conv_plan_s* p, const std::vector<long>& key, size_t n,
+                                 const std::function<void(float2*)>& fill, const float2** out, hipStream_t s) {
+  return find_or_make(p, key, s, out, [&](float2** d) {
+    const bl_status_t st = allocate(d, n);
+    if (st != BL_OK) return st;
+    fill(*d);
+    // (waited for: a call on another stream may be the next to read it)
+    return hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess ? BL_OK : BL_ERR_HIP;
+  });
 }
 
 bl_status_t lds_opt_in(const void* kern, int bytes) {

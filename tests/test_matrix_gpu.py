@@ -154,6 +154,25 @@ def test_matrix_transforms_keep_planes_apart(torch):
         assert torch.equal(yu, y0) and torch.isnan(yb[0])
 
 
+def test_tables_are_held_once(torch):
+    """A series layer's transforms keep one table for the samples it takes and
+    one for the samples it gives, whatever their place on the grid."""
+    dev = torch.device("cuda:0")
+    plan = blconv.Plan(1, 2, 2, 2, (2048,), 3, (1, 1), 0.0)
+    ws = plan.workspace(dev)
+    x, w, dy = (torch.randn(s, device=dev) for s in (plan.x_shape(), plan.w_shape(), plan.y_shape()))
+    y, dx, dw = torch.empty_like(dy), torch.empty_like(x), torch.empty_like(w)
+    torch.cuda.synchronize()
+    before = torch.cuda.mem_get_info(dev)[0]
+    plan.forward(x, w, y, ws)
+    plan.backward(dy, None, None, dx, dw, ws, flags=blconv.BL_REUSE_X | blconv.BL_REUSE_W)
+    torch.cuda.synchronize()
+    held = before - torch.cuda.mem_get_info(dev)[0]
+    one = 6 * plan.kept * 2048  # three bfloat16 of a cosine and a sine for a bin and two samples
+    say(f"[tables] {held / 1e6:.1f} MB held, {2 * one / 1e6:.1f} MB of two tables")
+    assert held <= 2 * one + (8 << 20)  # (tiles, the other tables, and memory given out in blocks of 2 MB)
+
+
 @pytest.mark.parametrize("nd,sp,K", [(2, (28, 21), 5), (2, (9, 9), 3), (1, (270,), 8), (1, (512,), 5), (1, (900,), 3)])
 def test_first_call_under_capture(torch, nd, sp, K):
     """A call captured before any table of its transforms is there (a table is
