@@ -673,13 +673,17 @@ bl_status_t launch_inv_wgrad_t(const bl_conv_plan_s* p, const float2* in, float*
   int slices, tc;
   size_t wlds;
   const float2* Et;
-  const bool sliced = wgrad_sliced_setup(p, wg, &wx, &slices, &wlds, &tc, &Et, s);
-  // two launches either way: the matrix product spares the slice sum's (64
-  // channels, 276 bins: 17.4 + 4.1 us here, 13.5 + 6.2 apart); with few
-  // channel pairs the slices cost the transform beside them nothing (3 x 16
-  // channels: 6.0 + 3.9 us here, 5.3 + 6.1 apart)
-  if (sliced && slices > 1 && (long)p->Cin * p->Cout >= 1024 && wgrad_by_product(p)) return BL_ERR_UNSUPPORTED;
-  if (!sliced) {
+  // Two launches either way: a matrix product apart spares the slice sum's, but
+  // the slices run in the transform's shadow until its planes fill the chip by
+  // themselves.  Combined backward call with 276 bins, here / product apart: 32
+  // channels, 16 images 16.2 / 18.0 us, 128 images 29.0 / 30.7; 64 channels, 16
+  // images 23.7 / 24.4, 64 images 30.6 / 32.5, 96 36.9 / 36.6, 128 41.4 / 41.2 and,
+  // with new inputs in every pass, 2.2 us more here; 96 channels, 16 images 34.2 /
+  // 36.1, 128 images 76 / 76.
+  if (P >= 6144 && (long)p->Cin * p->Cout >= 4096 && wgrad_by_product(p) && p->wg_chunks > 1 && p->wg_groups == 0 &&
+      !wgrad_wide(p))
+    return BL_ERR_UNSUPPORTED;
+  if (!wgrad_sliced_setup(p, wg, &wx, &slices, &wlds, &tc, &Et, s)) {
     // the wide one-pass body
     if (!wgrad_wide(p) || wgrad_table(p, &Et, s) != BL_OK) return BL_ERR_UNSUPPORTED;
     const long Q = (long)p->Cin * p->Cout;

@@ -154,6 +154,34 @@ def test_matrix_transforms_keep_planes_apart(torch):
         assert torch.equal(yu, y0) and torch.isnan(yb[0])
 
 
+def launches(torch, plan, call):
+    """Names of the kernels that `call` launches, and its x, w, dy (random)."""
+    dev = torch.device("cuda:0")
+    ws = plan.workspace(dev)
+    x, w, dy = (torch.randn(s, device=dev) for s in (plan.x_shape(), plan.w_shape(), plan.y_shape()))
+    y, dx, dw = torch.empty_like(dy), torch.empty_like(x), torch.empty_like(w)
+    plan.forward(x, w, y, ws)
+    with blconv.Profile() as prof:
+        if call == "backward":
+            plan.backward(dy, None, None, dx, dw, ws, flags=blconv.BL_REUSE_X | blconv.BL_REUSE_W)
+        else:
+            plan.backward_weight(None, dy, dw, ws, flags=blconv.BL_REUSE_X)
+        torch.cuda.synchronize()
+    return [r[0] for r in prof.records()]
+
+
+def test_weight_gradient_beside_the_inverse(torch):
+    """On the FFT grids the combined backward call has its weight gradient's
+    inverse in the launch of the input gradient's; with many planes and channel
+    pairs a product of its own, before whose choice no other table is made."""
+    for N, ci, co, hw, c in ((2, 3, 16, 32, 0.5), (4, 32, 32, 32, 0.5), (95, 64, 64, 32, 0.5), (96, 64, 63, 32, 0.5),
+                             (2, 64, 64, 8, 0.5)):
+        names = launches(torch, blconv.Plan(2, N, ci, co, (hw, hw), 3, (1, 1, 1, 1), c), "backward")
+        assert "spec_inv_wgrad_2d" in names and "wgrad_idft" not in names, (N, ci, co, names)
+    names = launches(torch, blconv.Plan(2, 96, 64, 64, (32, 32), 3, (1, 1, 1, 1), 0.5), "backward")
+    assert "wgrad_idft" in names and "wgrad_reduce" not in names, names
+
+
 def test_tables_are_held_once(torch):
     """A series layer's transforms keep one table for the samples it takes and
     one for the samples it gives, whatever their place on the grid."""
