@@ -679,9 +679,9 @@ bl_status_t launch_inv_wgrad_t(const bl_conv_plan_s* p, const float2* in, float*
   // channels, 16 images 16.2 / 18.0 us, 128 images 29.0 / 30.7; 64 channels, 16
   // images 23.7 / 24.4, 64 images 30.6 / 32.5, 96 36.9 / 36.6, 128 41.4 / 41.2 and,
   // with new inputs in every pass, 2.2 us more here; 96 channels, 16 images 34.2 /
-  // 36.1, 128 images 76 / 76.
-  if (P >= 6144 && (long)p->Cin * p->Cout >= 4096 && wgrad_by_product(p) && p->wg_chunks > 1 && p->wg_groups == 0 &&
-      !wgrad_wide(p))
+  // 36.1, 128 images 76 / 76.  435 bins, 64 channels, 128 images 48.1 / 49.2.
+  if (P >= 6144 && (long)p->Cin * p->Cout >= 4096 && p->kept <= 320 && wgrad_by_product(p) && p->wg_chunks > 1 &&
+      p->wg_groups == 0 && !wgrad_wide(p))
     return BL_ERR_UNSUPPORTED;
   if (!wgrad_sliced_setup(p, wg, &wx, &slices, &wlds, &tc, &Et, s)) {
     // the wide one-pass body

@@ -169,10 +169,16 @@ __device__ __forceinline__ void wgrad_wide_block(const float2* __restrict__ DW, 
 // The inverse DFT runs as one matrix product (launch_pgemm_inv): filters of
 // more than 9 taps (64 x 64 channels, 5 x 5, 184 bins 19.0 -> 4.6 us with the
 // slice sum; 256 x 256, 7 x 7, 276 bins 208 -> 65), and small filter banks with
-// few bins (3 x 3, 64 x 64 channels, 276 bins 9.6 -> 6.2, 612 bins 11.0 -> 11.7;
-// 256 x 256, 28 bins 6.8 -> 9.0).
+// few bins.  Weight-gradient call with stored spectra, product / slices and their
+// sum (one pass where bins are few), us: 3 x 3 taps, 64 x 64 channels, 264 bins
+// 13.7 / 17.1, 480 bins 18.2 / 23.1, 1104 bins 28.0 / 27.9; 3 x 16, 544 bins 11.8 /
+// 13.7, 840 bins 14.3 / 13.5; 100 x 100, 364 bins 27.0 / 30.1; 128 x 128, 144 bins
+// 21.3 / 22.6, 231 bins 25.3 / 25.2, 364 bins 29.3 / 29.9.  3 taps: 64 x 64, 452
+// bins 17.9 / 19.8; 32 x 64, 452 bins 14.7 / 14.5, 502 bins 15.2 / 13.9; 128 x 128,
+// 302 bins 29.2 / 26.6.
 inline bool wgrad_by_product(const bl_conv_plan_s* p) {
-  return p->Kh * p->Kw > 9 || ((long)p->Cin * p->Cout <= 16384 && p->kept <= 320);
+  const long pairs = (long)p->Cin * p->Cout;
+  return p->Kh * p->Kw > 9 || (pairs <= 10240 && p->kept <= 448) || (pairs <= 16384 && p->kept <= 256);
 }
 // The one-pass wide path applies to a plan (see launch_wgrad_idft).
 bool wgrad_wide(const bl_conv_plan_s* p);

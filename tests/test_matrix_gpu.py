@@ -182,6 +182,28 @@ def test_weight_gradient_beside_the_inverse(torch):
     assert "wgrad_idft" in names and "wgrad_reduce" not in names, names
 
 
+@pytest.mark.parametrize("nd,N,ci,co,sp,K,c,product", [
+    (2, 2, 32, 32, (26, 26), 3, 0.0, True),     # 420 bins
+    (1, 2, 80, 128, (893,), 3, 0.0, True),      # 10240 channel pairs, 448 bins
+    (1, 2, 80, 128, (895,), 3, 0.0, False),     # 449 bins
+    (1, 2, 80, 129, (599,), 3, 0.0, False),     # one pair of channels more, 301 bins
+    (1, 2, 120, 136, (509,), 3, 0.0, True),     # 16320 pairs, 256 bins
+    (1, 2, 120, 136, (511,), 3, 0.0, False),    # 257 bins
+    (1, 2, 2, 3, (1400,), 3, 0.0, False),       # 702 bins
+])
+def test_weight_gradient_by_product(torch, nd, N, ci, co, sp, K, c, product):
+    """Bounds of the product that takes the place of the sliced weight-gradient
+    inverse, each side against the oracle."""
+    layer = synth.Layer("wgp", nd, N, ci, co, sp[0], sp[1] if nd == 2 else 1, K, (1, 1) * nd, "blur")
+    plan = blconv.plan_for_layer(layer, c)
+    names = launches(torch, plan, "weight")
+    assert ("wgrad_reduce" not in names) == product, (plan.kept, names)
+    x, w, dy = synth.random_inputs(layer, 4700 + ci)
+    errs = [rel(g, r) for g, r in zip(gpu_passes(torch, layer, c, x, w, dy)[:3], oracle_passes(layer, c, x, w, dy))]
+    say(f"[wgrad product] {ci}->{co} @{sp} {plan.kept} bins: {errs}")
+    assert max(errs) <= FP32_TOL, errs
+
+
 def test_tables_are_held_once(torch):
     """A series layer's transforms keep one table for the samples it takes and
     one for the samples it gives, whatever their place on the grid."""
