@@ -479,8 +479,16 @@ bl_status_t launch_contract_tiled(const bl_conv_plan_s* p, Contract which, const
 
 bl_status_t launch_contract_bwd_pair(const bl_conv_plan_s* p, const void* DY, const void* W, float2* DX,
                                      const void* X, float2* DW, hipStream_t s) {
-  // with one or two images one launch of mostly empty tiles still takes less than two on the vector ALUs
-  if (p->N > 2 && (contract_is_thin(p, Contract::GradInput) || contract_is_thin(p, Contract::GradWeight)))
+  // With two images one launch of mostly empty tiles takes less than two where
+  // one is thin (3 x 16 channels, 480 bins 17.3 / 21.2 us of the combined call
+  // with stored spectra, 1740 bins 28.0 / 28.8); with one image, where both are,
+  // while bins and products are few: 16 x 16, 544 bins 20.2 / 21.0, 684 bins 23.5 /
+  // 22.1, 1740 bins 30.5 / 26.3; 64 x 64, 544 bins 34.9 / 34.8, 1002 bins 47.2 /
+  // 43.2; 128 x 128, 252 bins 36.9 / 37.7, 480 bins 56.5 / 50.3; 256 x 256, 91 bins
+  // 44.1 / 51.0, 252 bins 92 / 78; 512 x 512, 51 bins 73.7 / 83.8, 91 bins 142 / 140.
+  const long products = (long)p->kept * p->Cin * p->Cout;
+  const bool few = p->N == 2 || (p->N == 1 && (p->kept <= 96 || (p->kept <= 640 && products <= 6000000)));
+  if (!few && (contract_is_thin(p, Contract::GradInput) || contract_is_thin(p, Contract::GradWeight)))
     return BL_ERR_UNSUPPORTED;
   CgemmArgs g1, g2;
   bool v1, v2;

@@ -204,6 +204,33 @@ def test_weight_gradient_by_product(torch, nd, N, ci, co, sp, K, c, product):
     assert max(errs) <= FP32_TOL, errs
 
 
+@pytest.mark.parametrize("N,ci,co,nd,sp,paired", [
+    (1, 16, 16, 1, (1277,), True),      # 640 bins
+    (1, 16, 16, 1, (1279,), False),     # 641 bins
+    (1, 128, 144, 1, (649,), False),    # 326 bins, 6008832 products
+    (1, 128, 144, 1, (645,), True),     # 324 bins, 5971968 products
+    (1, 256, 256, 1, (189,), True),     # 96 bins
+    (1, 256, 256, 1, (191,), False),    # 97 bins
+    (2, 3, 16, 1, (1399,), True),       # two images, 701 bins
+])
+def test_one_image_pairs_few_products(torch, N, ci, co, nd, sp, paired):
+    """Bounds of the paired backward launch with one image, whose contractions
+    run on the vector ALUs else; each side against the oracle."""
+    layer = synth.Layer("pairs", nd, N, ci, co, sp[0], 1, 3, (1, 1) * nd, "walk")
+    plan = blconv.plan_for_layer(layer, 0.0)
+    names = launches(torch, plan, "backward")
+    assert ("contract_bwd" in names) == paired and ("contract_dgrad" in names) != paired, (plan.kept, names)
+    x, w, dy = synth.random_inputs(layer, 4800 + ci)
+    ws = plan.workspace(torch.device("cuda:0"))
+    xt, wt, dyt = (torch.from_numpy(a).to(ws.device) for a in (x, w, dy))
+    dx, dw = torch.full_like(xt, float("nan")), torch.full_like(wt, float("nan"))
+    plan.backward(dyt, wt, xt, dx, dw, ws)
+    torch.cuda.synchronize()
+    errs = [rel(g.cpu().numpy(), r) for g, r in zip((dx, dw), oracle_passes(layer, 0.0, x, w, dy)[1:])]
+    say(f"[one image] {ci}->{co} @{sp} {plan.kept} bins: {errs}")
+    assert max(errs) <= FP32_TOL, errs
+
+
 def test_tables_are_held_once(torch):
     """A series layer's transforms keep one table for the samples it takes and
     one for the samples it gives, whatever their place on the grid."""
