@@ -151,6 +151,27 @@ extern "C" bl_status_t bl_conv_plan_create(bl_conv_plan_t* out, const bl_conv_de
       while (p->fwd_split < 4 && st0 % (2 * p->fwd_split) == 0 && st0 / p->fwd_split >= 32 &&
              tiles0 * p->fwd_split <= 512)
         p->fwd_split *= 2;
+    // On the vector ALUs instead (forward pass with stored spectra, us, split
+    // tiles / those):
+    //  - one or two images: past one tile per CU, where a tile has one wave group
+    //    (512 -> 256, 28 bins 16.3 / 12.5, 45 bins 31.4 / 18.9; two images, 768 ->
+    //    512, 15 bins 19.4 / 27.5, 28 bins 40.6 / 28.6; 1024 -> 16, 45 bins 20.7 /
+    //    25.2, 66 bins 31.7 / 24.0), but for sums of 2048 (-> 16, 120 bins 49.0 /
+    //    57.7); and one image of fewer than 768 channels (512 -> 64, 6 bins 13.0 /
+    //    11.5; 768 -> 256, 28 bins 20.1 / 25.0) onto more than 32 (512 -> 16, 28
+    //    bins 12.8 / 15.0);
+    //  - one or two output channels (128 images, 512 -> 1, 120 bins 31.1 / 15.8;
+    //    2048 -> 2 65.1 / 59.3), three or four of few rows (1024 -> 4, 64 images,
+    //    120 bins 36.4 / 25.9; 128 images, 120 bins 40.6 / 42.3, 231 bins 61.6 /
+    //    76.1), five to eight of fewer (512 -> 8, 16 images, 45 bins 15.1 / 11.1; 64
+    //    images, 6 bins 13.3 / 11.2, 45 bins 16.6 / 17.8; 2048 -> 8, 16 images, 6
+    //    bins 17.6 / 20.5).
+    if (bl_contract_thin(p->N, p->Cout, p->Cin, p->kept, false, false)) {
+      const long rows = p->kept * p->N;
+      const bool row = (tiles0 * p->fwd_split > 256 && p->Cin < 2048) || (p->N == 1 && p->Cin < 768 && p->Cout > 32);
+      const bool col = p->Cout <= 2 || (p->Cout <= 4 && rows <= 8192) || (rows <= 1536 && p->Cin < 2048);
+      if (p->N <= 2 ? row : col) p->fwd_split = 1;
+    }
     p->fwd_ks = bl_contract_groups(t0.bm, t0.bn, tiles0 * p->fwd_split, st0 / p->fwd_split, p->bf16);
   }
   // partial sums of the weight-gradient inverse DFT over bin slices: enough

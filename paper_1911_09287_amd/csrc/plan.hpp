@@ -48,6 +48,37 @@ inline BlContractTiling bl_contract_tiling(long M, long N, long K, long bins, bo
   return t;
 }
 
+// Whether the contraction [M x K] . [K x N] over B bins (dgrad, wgrad: the
+// input and the weight gradient's) runs on the vector ALUs (thin.hip).
+inline bool bl_contract_thin(long M, long N, long K, long B, bool dgrad, bool wgrad) {
+  // Against the tiled kernels, whose matrix tiles are mostly padding here but
+  // whose loads are wide and whose sums run beside each other (us, thin / tiled,
+  // at 14, 101 and 1001 bins unless said):
+  //  - outer products (K = 1): 64 x 128 4.3 / 4.5 and 14.7 / 19.0.  K = 2: 32 x
+  //    128 12.4 / 13.4 at 1001 bins; 2 x 256 x 256 of a gradient 160 / 135;
+  if (K == 1 || (K == 2 && !wgrad)) return true;
+  //  - one or two rows: 64 -> 64 3.9 / 5.7, 4.2 / 5.9, 6.7 / 11.0; two rows 81 ->
+  //    100 4.9 / 8.5 at 51 bins, 17.1 / 25.9 at 1001, 256 -> 256 102 / 94 at 546.
+  //    The input gradient's lanes walk rows of W one element apart in k: 4.1 /
+  //    5.3, 4.4 / 5.7, then 13.6 / 9.9, and 256 -> 256 11.0 / 9.1, 215 / 116;
+  if (M <= 2) return B * N * K <= (dgrad ? 500000 : 20000000);
+  //  - one or two columns, a wave per row: 64 rows of 128 4.1 / 6.9, 4.1 / 7.3,
+  //    15.7 / 16.1; 128 rows of 64 4.2 / 6.1 at 51 bins, 19.3 / 13.1 at 546.  The
+  //    weight gradient's lanes read A one row apart: 128 rows of 64 4.1 / 6.4,
+  //    6.7 / 6.4, 49.7 / 19.9;
+  //  - three to eight columns while rows are few, the more the longer: 64 rows of
+  //    64 4.2 / 5.7, 5.6 / 5.9, 31.9 / 9.7; 16 rows of 352 5.5 / 10.7, 7.0 / 11.0,
+  //    30 / 34.
+  // Three rows or products and more: tiled throughout (M = 8, 512 x 512 136 / 16
+  // at 14 bins; M = 3, 64 x 64 11.9 / 6.1 at 51; K = 3, 64 x 64 4.4 / 4.5, 5.5 /
+  // 5.1, 15.1 / 11.0).
+  // (few columns with few rows or products would leave the lanes of k_thin_cols
+  // idle: 6 x 2, 114 products, 36 bins 28.8)
+  if (N > 8 || M <= 8 || K <= 8) return false;
+  if (N <= 2) return B * M <= (wgrad ? 8192 : 32768);
+  return B * M <= (64 * K > 8192 ? 64 * K : 8192);
+}
+
 struct bl_conv_plan_s {
   bl_conv_desc_t desc;
   int ndim;

@@ -73,6 +73,32 @@ def test_grid_override_worked_example():
     assert round(100 * plan.c_eff, 2) == 6.61
 
 
+def _areas(plan):
+    """Bytes of the workspace without partial spectra: X, W, DY, the spectrum of
+    the larger side, DW and the sliced weight-gradient inverse's sums."""
+    B, N, ci, co, T = plan.kept, plan.N, plan.C_in, plan.C_out, plan.K ** plan.ndim
+    up = lambda n: (n + 255) // 256 * 256
+    blocks = (ci * co + 255) // 256
+    per = max(16, -(-B // -(-1024 // blocks)))
+    per = min((per + 7) // 8 * 8, 48 * 1024 // (T * 8) // 8 * 8)
+    slices = -(-B // per)
+    part = slices * ci * co * T * 4 if slices > 1 else 0
+    return sum(up(8 * n) for n in (B * N * ci, B * ci * co, B * N * co, B * N * max(ci, co), B * ci * co)) + up(part)
+
+
+@pytest.mark.parametrize("N,ci,co,hw,parts", [
+    (1, 512, 128, 4, 1), (1, 512, 32, 4, 2), (1, 768, 128, 4, 2),  # one image: fewer than 768 channels onto more than 32
+    (2, 768, 240, 8, 2), (2, 768, 240, 13, 1), (2, 512, 128, 4, 2),  # 224 and 360 split tiles
+    (1, 2048, 16, 20, 4), (3, 512, 240, 13, 2),  # long sums; three images: tiles throughout
+    (128, 512, 2, 20, 1), (64, 512, 4, 20, 1), (69, 512, 3, 20, 2), (16, 512, 8, 13, 1), (64, 512, 8, 8, 2),
+    (16, 2048, 8, 4, 4), (16, 512, 9, 4, 2),  # few output channels
+])
+def test_forward_split_leaves_few_rows_or_columns_to_the_vector_kernel(N, ci, co, hw, parts):
+    plan = blconv.Plan(2, N, ci, co, (hw, hw), 3, (1, 1, 1, 1), 0.5)
+    spectra = parts * plan.kept * N * co * 8 if parts > 1 else 0
+    assert plan.workspace_bytes - _areas(plan) == (spectra + 255) // 256 * 256
+
+
 def test_bins_order_is_documented_order():
     for (Lh, Lw, c) in ((34, 34, 0.5), (9, 7, 0.3), (6, 6, 0.75), (1, 519, 0.25)):
         if Lh == 1:
