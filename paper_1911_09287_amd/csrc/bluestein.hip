@@ -480,22 +480,15 @@ bl_status_t launch_1k(const bl_conv_plan_s* p, const BlueGeom& a0, const void* i
   }
 }
 
-int fft_size_for(int need) {
-  int M = 256;
-  while (M < need) M *= 2;
-  return M;
-}
-
 // The chirp convolution takes an FFT of 1024 points and no fewer (shorter ones
 // are slower than one matrix product), and whether two series share one (when
-// the conjugate-symmetric output or input range fits the same FFT size).
+// the conjugate-symmetric output or input range fits it as well).
 bool takes_1k(int L, int V, long P, int other, bool* pack) {
-  if (2 * L > 64 * 64) return false;
-  if ((long)V * other < 2048) return false;  // the direct DFT is as cheap
-  const int M1 = fft_size_for(V + other - 1);
-  const int M2 = fft_size_for(2 * V - 1 + other - 1);
-  *pack = P >= 2 && 2 * (V - 1) < L && M2 <= M1 && M2 <= 1024;
-  return (*pack ? M2 : M1) == 1024;
+  const int points = V + other - 1;
+  if (2 * L > 64 * 64 || points <= 512 || points > 1024) return false;
+  if ((long)V * other < 2048) return false;  // a few bins: left to the matrix product
+  *pack = P >= 2 && 2 * (V - 1) < L && points + V - 1 <= 1024;
+  return true;
 }
 
 bl_status_t launch_any(const bl_conv_plan_s* p, BlueGeom& a, bool inv, int other, const void* in, void* out,

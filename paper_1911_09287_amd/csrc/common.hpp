@@ -178,11 +178,11 @@ bl_status_t launch_fft2_fwd(const bl_conv_plan_s* p, const float* in, void* out,
 bl_status_t launch_fft2_inv(const bl_conv_plan_s* p, const float2* in, float* out, long P, int OH, int OW, int ci,
                             int cj, hipStream_t s, int nsplit = 1, size_t pstride = 0);
 // Transforms of series and small planes as one product with a root table of
-// 2 kept x samples entries (at most 64 MB, a plan table).  filters > 0: the
+// kept x samples entries (at most 64 MB, a plan table).  filters > 0: the
 // planes are the (c, f) pairs of a filter bank of that many filters, samples
 // [f][c][taps], spectrum [bin][c][f].
 bl_status_t launch_pgemm_fwd(const bl_conv_plan_s* p, const float* in, void* out, long P, int Hin, int Win, int oi,
-                             int oj, hipStream_t s, int filters = 0);
+                             int oj, hipStream_t s);
 bl_status_t launch_pgemm_inv(const bl_conv_plan_s* p, const float2* in, float* out, long P, int OH, int OW, int ci,
                              int cj, hipStream_t s, int nsplit = 1, size_t pstride = 0, int filters = 0);
 // 2-D transforms of any grid (sides up to 128 samples, 64 kept columns) as

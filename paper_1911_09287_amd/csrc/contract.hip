@@ -454,9 +454,10 @@ bl_status_t launch_contract_tiled(const bl_conv_plan_s* p, Contract which, const
 #define BL_VEC(BMV, BNV, AK, BK, CJ, BF, KSV)                                                  \
   (vec ? go(k_cgemm<BMV, BNV, AK, BK, CJ, BF, true, KSV>, Tile<BMV, BNV, BF>::units, KSV)        \
        : go(k_cgemm<BMV, BNV, AK, BK, CJ, BF, !(AK || BK), KSV>, Tile<BMV, BNV, BF>::units, KSV))
-#define BL_TYPES(BMV, BNV, AK, BK, CJ, KSV)                                                             \
-  st = p->bf16 ? (t.ks > 1 ? BL_VEC(BMV, BNV, AK, BK, CJ, true, KSV) : BL_VEC(BMV, BNV, AK, BK, CJ, true, 1)) \
-               : (t.ks > 1 ? BL_VEC(BMV, BNV, AK, BK, CJ, false, KSV) : BL_VEC(BMV, BNV, AK, BK, CJ, false, 1))
+#define BL_TYPES(BMV, BNV, AK, BK, CJ, KSV)                      \
+  st = p->bf16    ? BL_VEC(BMV, BNV, AK, BK, CJ, true, 1)    \
+       : t.ks > 1 ? BL_VEC(BMV, BNV, AK, BK, CJ, false, KSV) \
+                  : BL_VEC(BMV, BNV, AK, BK, CJ, false, 1)
 #define BL_SHAPES(AK, BK, CJ)                                     \
   if (BM == 64 && BN == 64) BL_TYPES(64, 64, AK, BK, CJ, 2);      \
   else if (BM == 64 && BN == 32) BL_TYPES(64, 32, AK, BK, CJ, 4); \

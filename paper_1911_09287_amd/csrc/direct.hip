@@ -579,9 +579,8 @@ bl_status_t launch_spec_filt(const bl_conv_plan_s* p, const float* w, void* out,
 bool wgrad_wide(const bl_conv_plan_s* p) {
   const long Q = (long)p->Cin * p->Cout;
   const int B = (int)p->kept, T = p->Kh * p->Kw;
-  const int tmax_w = T <= 9 ? T : 16;
-  return (Q / 64 >= 256 || B <= 256) && p->Cout <= 256 && T <= 16 &&
-         (long)(B * tmax_w * sizeof(float2)) <= kWgradSliceLds && Q < 2147483647L;
+  return (Q / 64 >= 256 || B <= 256) && p->Cout <= 256 && T <= 9 && (long)(B * T * sizeof(float2)) <= kWgradSliceLds &&
+         Q < 2147483647L;
 }
 
 bl_status_t wgrad_table(const bl_conv_plan_s* p, const float2** Et, hipStream_t s) {
@@ -593,15 +592,14 @@ bool wgrad_sliced_setup(const bl_conv_plan_s* p, WgradGeom& g, long* xblocks, in
                         int* tc, const float2** Et, hipStream_t s) {
   g = WgradGeom{p->Cout, p->Cin, p->Kh, p->Kw, p->Kh * p->Kw, p->Lh, p->Lw, p->r_h, p->R, p->V, 0, 0,
                 (p->Cout + 15) / 16};
-  if (g.T > 64 || p->wg_groups > 0 || wgrad_wide(p)) return false;
+  if (g.T > 9 || p->wg_groups > 0 || wgrad_wide(p)) return false;
   const long Q = (long)p->Cin * p->Cout;
   g.chunks = p->wg_chunks;  // the workspace holds partial sums for this many slices
   g.bins_per_chunk = p->wg_bins;
   if (g.chunks > 65535) return false;
-  const int tmax = g.T <= 9 ? g.T : g.T <= 16 ? 16 : g.T <= 32 ? 32 : 64;  // as instantiated
-  *lds = (size_t)g.bins_per_chunk * tmax * sizeof(float2);
+  *lds = (size_t)g.bins_per_chunk * g.T * sizeof(float2);
   if ((long)*lds > kWgradSliceLds) return false;
-  const int TC = chan_tile(g.T, p->Cout), TF = kThreads / TC;
+  const int TC = chan_tile(p->Cout), TF = kThreads / TC;
   *tc = TC;
   *xblocks = TC == 1 ? (Q + kThreads - 1) / kThreads : (long)((p->Cin + TC - 1) / TC) * ((p->Cout + TF - 1) / TF);
   *slices = g.chunks;
@@ -622,26 +620,25 @@ bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* 
   if (wgrad_by_product(p)) {
     const bl_status_t st = launch_pgemm_inv(p, DW, dw, (long)p->Cin * p->Cout, p->Kh, p->Kw, 0, 0, s, 1, 0, p->Cout);
     if (st != BL_ERR_UNSUPPORTED) return st;
+    if (p->Kh * p->Kw > 9) return BL_ERR_OOM;  // no memory for its table, or none to be had during a capture
   }
   WgradGeom g{p->Cout, p->Cin, p->Kh, p->Kw, p->Kh * p->Kw, p->Lh, p->Lw, p->r_h, p->R, p->V, 0, 0,
               (p->Cout + 15) / 16};
   const long Q = (long)p->Cin * p->Cout;
   const int B = (int)p->kept;
-  const int tmax_w = g.T <= 9 ? g.T : 16;
   const bool wide = wgrad_wide(p);
   // one pass over all bins when there are at least 256 blocks of 64 pairs,
   // or few bins (at most 256: a sixteenth per wave), and taps and table fit
   // (rows of at most 256 output channels: wider rows write dw better from the
   // tiled kernel below); otherwise bin slices and a fixed-order sum
-  if (g.T > 64) return BL_ERR_UNSUPPORTED;
   const float2* Et = nullptr;  // E[bin][t], built once per plan
   const bl_status_t ts = wgrad_table(p, &Et, s);
-  if (ts != BL_OK) return ts;
+  if (ts != BL_OK) return ts == BL_ERR_UNSUPPORTED ? BL_ERR_OOM : ts;
   if (p->wg_groups > 0) {  // 16 x 16 channel tiles over all bins
-    const int tmax = wgrad_tmax(g.T), NG = p->wg_groups;
+    const int NG = p->wg_groups;
     g.bins_per_chunk = B;
     g.chunks = 1;
-    const size_t lds = (size_t)B * tmax * sizeof(float2) + (size_t)NG * 256 * tmax * sizeof(float);
+    const size_t lds = (size_t)B * g.T * sizeof(float2) + (size_t)NG * 256 * g.T * sizeof(float);
     const long tiles = (long)((p->Cin + 15) / 16) * g.tiles_f;
     const double bytes = (double)Q * B * 8 + (double)Q * g.T * 4;
     bl_status_t st = BL_ERR_UNSUPPORTED;
@@ -655,18 +652,16 @@ bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* 
       });
     };
 #define BL_WG(TM)                                                                                            \
-  case TM:                                                                                                   \
-    st = NG == 4 ? go(k_wgrad_tile<TM, 4>, 4) : NG == 2 ? go(k_wgrad_tile<TM, 2>, 2) : go(k_wgrad_tile<TM, 1>, 1); \
-    break;
-    switch (tmax) {
-      BL_WG(1) BL_WG(2) BL_WG(3) BL_WG(4) BL_WG(5) BL_WG(6) BL_WG(7) BL_WG(8) BL_WG(9) BL_WG(16)
+  case TM: st = NG == 4 ? go(k_wgrad_tile<TM, 4>, 4) : go(k_wgrad_tile<TM, 2>, 2); break;
+    switch (g.T) {
+      BL_WG(1) BL_WG(2) BL_WG(3) BL_WG(4) BL_WG(5) BL_WG(6) BL_WG(7) BL_WG(8) BL_WG(9)
       default: return BL_ERR_UNSUPPORTED;
     }
 #undef BL_WG
     return st;
   }
   if (wide) {
-    const size_t lds = (size_t)B * tmax_w * sizeof(float2);
+    const size_t lds = (size_t)B * g.T * sizeof(float2);
     const long blocks = (Q + 63) / 64;
     // at most one block per CU: 16 waves per block, each over a sixteenth of
     // the bins, so that every SIMD still holds several waves (measured: with
@@ -686,17 +681,16 @@ bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* 
   case t: return many ? go(k_wgrad_wide<t, 16>, 16) : go(k_wgrad_wide<t, 4>, 4);
     switch (g.T) {
       BL_WIDE(1) BL_WIDE(2) BL_WIDE(3) BL_WIDE(4) BL_WIDE(5) BL_WIDE(6) BL_WIDE(7) BL_WIDE(8) BL_WIDE(9)
-      default: return many ? go(k_wgrad_wide<16, 16>, 16) : go(k_wgrad_wide<16, 4>, 4);
+      default: return BL_ERR_UNSUPPORTED;
     }
 #undef BL_WIDE
   }
   g.chunks = p->wg_chunks;  // the workspace holds partial sums for this many slices
   g.bins_per_chunk = p->wg_bins;
   if (g.chunks > 65535) return BL_ERR_UNSUPPORTED;
-  const int tmax = g.T <= 9 ? g.T : g.T <= 16 ? 16 : g.T <= 32 ? 32 : 64;  // as instantiated below
-  const size_t lds = (size_t)g.bins_per_chunk * tmax * sizeof(float2);
+  const size_t lds = (size_t)g.bins_per_chunk * g.T * sizeof(float2);
   if ((long)lds > kWgradSliceLds) return BL_ERR_UNSUPPORTED;
-  const int TC = chan_tile(g.T, p->Cout), TF = kThreads / TC;
+  const int TC = chan_tile(p->Cout), TF = kThreads / TC;
   const long xblocks = TC == 1 ? (Q + kThreads - 1) / kThreads : (long)((p->Cin + TC - 1) / TC) * ((p->Cout + TF - 1) / TF);
   dim3 grid((unsigned)xblocks, (unsigned)g.chunks);
   const double bytes = (double)Q * B * 8 + (double)Q * g.T * 4;
@@ -712,10 +706,7 @@ bl_status_t launch_wgrad_idft(const bl_conv_plan_s* p, const float2* DW, float* 
   case n: st = go2(k_wgrad_idft<n, 8>, k_wgrad_idft<n, 1>); break;
     BL_WG_T(1) BL_WG_T(2) BL_WG_T(3) BL_WG_T(4) BL_WG_T(5) BL_WG_T(6) BL_WG_T(7) BL_WG_T(8) BL_WG_T(9)
 #undef BL_WG_T
-    default:
-      if (g.T <= 16) st = go2(k_wgrad_idft<16, 8>, k_wgrad_idft<16, 1>);
-      else if (g.T <= 32) st = go(k_wgrad_idft<32, 1>);
-      else st = go(k_wgrad_idft<64, 1>);
+    default: return BL_ERR_UNSUPPORTED;
   }
   if (st != BL_OK || g.chunks == 1) return st;
   return launch_wgrad_reduce(p, part, dw, g, s);

@@ -30,9 +30,7 @@
 #include <cmath>
 
 #include "common.hpp"
-#include "filt.hpp"
 #include "split.hpp"
-#include "wgrad.hpp"
 
 namespace blc {
 namespace {

@@ -35,7 +35,7 @@ struct PgemmArgs {
   int kept, n;         // bins; samples per plane
   int rows, steps;     // table rows (forward: bins, inverse: sample pairs); steps of 32 of the other
   int ctiles;          // groups of planes (blocks along the planes)
-  unsigned F;          // filters: plane (c, f) = c F + f of the spectrum is plane f (P / F) + c of the samples; 0: the same
+  unsigned F;          // inverse of a filter bank of F filters: plane (c, f) = c F + f of the spectrum is plane f (P / F) + c of the samples; 0: the same
   unsigned nsplit;             // inverse: partial spectra to add
   unsigned long long pstride;  // complex values between two partial spectra
   const uintx4* tab;   // [row tile][step][cosine, sine][part][lane]
@@ -313,7 +313,8 @@ bl_status_t pgemm_table(const bl_conv_plan_s* p, int H, int W, int oi, int oj, P
 template <bool INV, bool PARTS, typename S>
 bl_status_t pgemm_launch(const bl_conv_plan_s* p, const void* in, void* out, PgemmArgs g, double bytes, double flops,
                          hipStream_t s) {
-  const char* name = g.F ? (INV ? "wgrad_idft" : "spec_filt") : INV ? (p->Lh == 1 ? "spec_inv_1d" : "spec_inv_2d") : (p->Lh == 1 ? "spec_fwd_1d" : "spec_fwd_2d");
+  const char* name = g.F ? "wgrad_idft"
+                     : INV ? (p->Lh == 1 ? "spec_inv_1d" : "spec_inv_2d") : (p->Lh == 1 ? "spec_fwd_1d" : "spec_fwd_2d");
   const int rtiles = (g.rows + 15) / 16;
   auto go = [&](auto kern, int rm, int kw) {
     const int cols = 16 * (4 / kw);
@@ -342,15 +343,14 @@ bl_status_t pgemm_launch(const bl_conv_plan_s* p, const void* in, void* out, Pge
 }  // namespace
 
 bl_status_t launch_pgemm_fwd(const bl_conv_plan_s* p, const float* in, void* out, long P, int Hin, int Win, int oi,
-                             int oj, hipStream_t s, int filters) {
+                             int oj, hipStream_t s) {
   const long n = (long)Hin * Win;
   PgemmArgs g{};
   if (!pgemm_sizes<false>(p, P, n, g)) return BL_ERR_UNSUPPORTED;
-  g.F = (unsigned)filters;
   const bl_status_t st = pgemm_table<false>(p, Hin, Win, oi, oj, g, s);
   if (st != BL_OK) return st == BL_ERR_OOM ? BL_ERR_UNSUPPORTED : st;
   const double bytes = (double)P * n * 4 + (double)P * p->kept * (p->bf16 ? 4 : 8);
-  const double flops = filters ? 0.0 : (double)P * 2.5 * p->Lh * p->Lw * std::log2(std::max(2.0, (double)p->Lh * p->Lw));
+  const double flops = (double)P * 2.5 * p->Lh * p->Lw * std::log2(std::max(2.0, (double)p->Lh * p->Lw));
   return p->bf16 ? pgemm_launch<false, false, unsigned>(p, in, out, g, bytes, flops, s)
                  : pgemm_launch<false, false, float2>(p, in, out, g, bytes, flops, s);
 }

@@ -174,19 +174,21 @@ extern "C" bl_status_t bl_conv_plan_create(bl_conv_plan_t* out, const bl_conv_de
     }
     p->fwd_ks = bl_contract_groups(t0.bm, t0.bn, tiles0 * p->fwd_split, st0 / p->fwd_split, p->bf16);
   }
-  // partial sums of the weight-gradient inverse DFT over bin slices: enough
-  // slices for ~1024 blocks of 256 (c, f) pairs, at least 16 bins per slice,
-  // whole batches of 8 bins, and a slice's weights [bins][taps, padded as the
-  // kernels are instantiated] within kWgradSliceLds
-  {
+  // partial sums of the weight-gradient inverse DFT over bin slices (filters of
+  // up to 9 taps; larger ones take a matrix product): enough slices for ~1024
+  // blocks of 256 (c, f) pairs, at least 16 bins per slice, whole batches of 8
+  // bins, and a slice's weights [bins][taps] within kWgradSliceLds
+  p->wg_bins = (int)p->kept;
+  p->wg_chunks = 1;
+  p->wg_groups = 0;
+  p->off_Part = o;
+  const long T = (long)p->Kh * p->Kw;
+  if (T <= 9) {
     const long Q = (long)p->Cin * p->Cout;
-    const int T = p->Kh * p->Kw;
-    const long tmax = T <= 9 ? T : T <= 16 ? 16 : T <= 32 ? 32 : 64;
     const long xblocks = (Q + 255) / 256;
     const long want = (1024 + xblocks - 1) / xblocks;
     long per = std::max<long>(16, (p->kept + want - 1) / want);
-    const long cap = std::max<long>(8, kWgradSliceLds / (tmax * 8) / 8 * 8);
-    per = std::min((per + 7) / 8 * 8, cap);
+    per = std::min((per + 7) / 8 * 8, kWgradSliceLds / (T * 8) / 8 * 8);
     const long chunks = (p->kept + per - 1) / per;
     p->wg_bins = (int)per;
     p->wg_chunks = (int)chunks;
@@ -195,17 +197,11 @@ extern "C" bl_status_t bl_conv_plan_create(bl_conv_plan_t* out, const bl_conv_de
     // waves, the bins' weights and the groups' sums within 64 KB of LDS each.
     // With more tiles one group per tile would sum every bin in series; the
     // bin slices above split that work instead.
-    {
-      const long tiles = (long)((p->Cin + 15) / 16) * ((p->Cout + 15) / 16);
-      int ng = 2;
-      while (ng < 4 && tiles * ng * 4 < 2048) ng *= 2;
-      const int tm = wgrad_tmax(T);
-      p->wg_groups = (tiles < 512 && tiles * ng * 4 >= 2048 && T <= 16 && p->kept * tm * 8 <= 64 * 1024 &&
-                      (long)ng * 256 * tm * 4 <= 64 * 1024) ? ng : 0;
-    }
-    p->off_Part = o;
-    o = align_up(o + (chunks > 1 ? (size_t)chunks * Q * p->Kh * p->Kw * sizeof(float) : 0),
-                 256);
+    const long tiles = (long)((p->Cin + 15) / 16) * ((p->Cout + 15) / 16);
+    int ng = 2;
+    while (ng < 4 && tiles * ng * 4 < 2048) ng *= 2;
+    p->wg_groups = (tiles < 512 && tiles * ng * 4 >= 2048 && p->kept * T * 8 <= 64 * 1024) ? ng : 0;
+    if (chunks > 1) o = align_up(o + (size_t)chunks * Q * T * sizeof(float), 256);
   }
   // split-k partial tiles of the contraction (largest of the three passes and
   // of the paired backward launch)

@@ -16,7 +16,7 @@ namespace blc {
 // input channels, so that the gradient rows dw[f][c0 .. c0 + 8][taps] are
 // written 8 x taps floats at a time; otherwise a block spans whole rows of
 // one input channel.
-inline int chan_tile(int taps, int F) { return (taps <= 16 && F > 256) ? 8 : 1; }
+inline int chan_tile(int F) { return F > 256 ? 8 : 1; }
 
 struct WgradGeom {
   int F, C, Kh, Kw, T;
