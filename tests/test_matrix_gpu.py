@@ -2,11 +2,13 @@
 
 Sizes where a tile, stage or split ends, against the fp64 oracle.  fp32 bound:
 a sum of K complex products takes 12 K / 16 roundings of its accumulator, each
-0.29 x 2^-24 of the partial sum (RMS); over the 2050 products of the longest
-case these grow to 4.8e-7 of the result, and the transforms on either side add
+0.29 x 2^-24 of the partial sum (RMS); over 2050 products, were they one sum,
+these grow to 4.8e-7 of the result, and the transforms on either side add
 about 3e-7, so 1e-6 holds for every case while a dropped part of a split value
 (2^-9 to 2^-17 of it) does not.
 """
+import math
+
 import pytest
 
 from oracle import bl_oracle as bo
@@ -32,7 +34,7 @@ def torch():
     (32, 16, 32, 2, 0),    # exactly one 32 x 32 tile and one stage of 16 k
     (65, 48, 97, 3, 0),    # one row and one column past 64-wide tiles, three stages over two wave groups
     (33, 80, 31, 5, 0),    # 64 x 32 tiles, five stages over four wave groups
-    (9, 2050, 70, 1, 0),   # few tiles, long sums: k split, the last range two k long
+    (9, 2050, 70, 1, 0),   # few tiles, long sums: k split in 544, 544, 544 and 418
     (64, 1024, 64, 2, 0),  # forward split along k, its partial spectra added by the inverse
     (16, 512, 512, 4, 0),  # paired backward: grad-input split along k
     (130, 24, 64, 6, 0),   # paired backward: grad-weight with the longer sums, whole
@@ -56,6 +58,89 @@ def test_contraction_tiles(torch, N, ci, co, hw, bf16):
     ref = oracle_passes(layer, 0.0, x, w, dy, rounding=bo.round_bf16 if bf16 else None)
     errs = [rel(g, r) for g, r in zip(got[:3] + (dx.cpu().numpy(), dw.cpu().numpy()), ref + ref[1:])]
     say(f"[tiles] {N} {ci}->{co} @{hw} bf16={bf16}: {errs}")
+    assert max(errs) <= (BF16_TOL if bf16 else FP32_TOL), errs
+
+
+def test_last_range_of_one(torch):
+    """A sum split along k whose last range is one k long (less than a stage)."""
+    layer = synth.Layer("last_range", 2, 40, 7681, 40, 1, 1, 3, (1, 1, 1, 1), "blur")
+    x, w, _ = synth.random_inputs(layer, 4400)
+    plan = blconv.plan_for_layer(layer, 0.0)
+    dev = torch.device("cuda:0")
+    ws = plan.workspace(dev)
+    ws.fill_(0xFF)
+    y = torch.full(plan.y_shape(), float("nan"), device=dev)
+    with blconv.Profile() as prof:
+        plan.forward(torch.from_numpy(x).to(dev), torch.from_numpy(w).to(dev), y, ws)
+        torch.cuda.synchronize()
+    summed = [r[2] for r in prof.records() if r[0] == "contract_reduce"]
+    splits = round(summed[0] / (8 * plan.kept * layer.N * layer.C_out)) - 1
+    length = -(-(-(-layer.C_in // splits)) // 32) * 32
+    assert splits > 1 and layer.C_in - (splits - 1) * length == 1, splits
+    err = rel(y.cpu().numpy(), bo.forward(x, w, layer.pad, 0.0))
+    say(f"[last range] {splits} ranges: {err}")
+    assert err <= FP32_TOL, err
+
+
+@pytest.mark.parametrize("ci,co,sp,c,call", [
+    (512, 64, (20, 20), 0.5, "forward"),  # one step of 32 rows and of 32 (column, part)
+    (512, 64, (6, 60), 0.0, "forward"),   # one and two
+    (512, 63, (4, 100), 0.0, "forward"),  # one and four
+    (512, 64, (80, 6), 0.0, "forward"),   # two and one
+    (64, 512, (21, 18), 0.5, "backward"),  # grad-input in four parts
+])
+def test_two_product_inverse_adds_partial_spectra(torch, ci, co, sp, c, call):
+    """The two-product 2-D inverse adds the partial spectra of a contraction
+    split along k as it loads them."""
+    layer = synth.Layer("parts", 2, 15, ci, co, *sp, 3, (1, 1, 1, 1), "blur")
+    x, w, dy = synth.random_inputs(layer, 4450 + sp[0])
+    plan = blconv.plan_for_layer(layer, c)
+    dev = torch.device("cuda:0")
+    ws = plan.workspace(dev)
+    ws.fill_(0xFF)
+    xt, wt, dyt = (torch.from_numpy(a).to(dev) for a in (x, w, dy))
+    plan.forward(xt, wt, torch.empty_like(dyt), ws)
+    out = torch.full_like(dyt if call == "forward" else xt, float("nan"))
+    with blconv.Profile() as prof:
+        if call == "forward":
+            plan.forward(None, None, out, ws, flags=blconv.BL_REUSE_X | blconv.BL_REUSE_W)
+        else:
+            plan.backward(dyt, None, None, out, torch.empty_like(wt), ws, flags=blconv.BL_REUSE_X | blconv.BL_REUSE_W)
+        torch.cuda.synchronize()
+    names = [r[0] for r in prof.records()]
+    planes, points = 15 * min(ci, co), plan.fft[0] * plan.fft[1]
+    (nbytes, flops), = [r[2:] for r in prof.records() if r[0] == "spec_inv_2d"]
+    parts = (nbytes - 4 * planes * sp[0] * sp[1]) / (8 * planes * plan.kept)
+    assert parts >= 2 and "contract_reduce" not in names, (parts, names)
+    assert abs(flops - planes * 2.5 * points * math.log2(points)) > 1.0  # (what the single product reports)
+    want = bo.forward(x, w, layer.pad, c) if call == "forward" else bo.backward_input(dy, w, sp, layer.pad, c)
+    err = rel(out.cpu().numpy(), want)
+    say(f"[parts] {ci}->{co} @{sp}: {parts:.0f} parts, {err}")
+    assert err <= FP32_TOL, err
+
+
+@pytest.mark.parametrize("N,ci,co,c,shared,bf16", [
+    (17, 179, 181, 0.5, True, 0), (17, 179, 181, 0.5, True, 1),  # two series to a transform: 3043 and 3077
+    (9, 175, 177, 0.0, False, 0), (9, 175, 177, 0.0, False, 1),  # one each: 1575 and 1593
+])
+def test_many_series_by_chirp_z(torch, N, ci, co, c, shared, bf16):
+    """Series past the product's bound, in odd numbers: the chirp-z kernel's
+    last half-wave, and its last transform with one series of two."""
+    layer = synth.Layer("chirp", 1, N, ci, co, 515, 1, 3, (1, 1), "walk")
+    x, w, dy = synth.random_inputs(layer, 4900 + N)
+    flags = blconv.BL_DESC_BF16_SPECTRA if bf16 else 0
+    got = gpu_passes(torch, layer, c, x, w, dy, desc_flags=flags)
+    plan, ws = got[3], got[4]
+    xt, wt = torch.from_numpy(x).to(ws.device), torch.from_numpy(w).to(ws.device)
+    with blconv.Profile() as prof:
+        plan.forward(xt, wt, torch.empty(plan.y_shape(), device=ws.device), ws)
+        torch.cuda.synchronize()
+    for name, series in (("spec_fwd_1d", N * ci), ("spec_inv_1d", N * co)):
+        (flops,) = [r[3] for r in prof.records() if r[0] == name]
+        assert flops == (series // 2 + 1 if shared else series) * 100.0 * 1024, (name, flops)
+    ref = oracle_passes(layer, c, x, w, dy, rounding=bo.round_bf16 if bf16 else None)
+    errs = [rel(g, r) for g, r in zip(got[:3], ref)]
+    say(f"[chirp-z] {N} {ci}->{co} c{c} bf16={bf16}: {errs}")
     assert max(errs) <= (BF16_TOL if bf16 else FP32_TOL), errs
 
 

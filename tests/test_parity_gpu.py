@@ -200,9 +200,8 @@ def test_largest_grids(torch):
 
 
 def test_1d_long_sequences(torch):
-    """1-D lengths that take the chirp-z (Bluestein) path with FFT sizes 256,
-    512 and 1024, odd and even grids, offsets, grid overrides, and lengths
-    beyond it (direct DFT path)."""
+    """1-D lengths from 60 to 700, odd and even grids, offsets and grid
+    overrides (few series: transforms as matrix products)."""
     rng = np.random.default_rng(77)
     for i in range(16):
         L = int(rng.integers(60, 700))
@@ -223,9 +222,9 @@ def test_1d_long_sequences(torch):
 
 def test_1d_many_series(torch):
     """1-D layers with thousands of series, so that waves of the chirp-z kernel
-    run more than one round: inputs longer than 512 (each round loaded when it
-    starts) and shorter ones (the next round loaded during the current one),
-    forward and inverse, paired and single series."""
+    run more than one round (each round loaded when it starts): forward and
+    inverse, paired and single series; and the matrix product of 300 samples
+    with as many."""
     cases = [
         (synth.Layer("rounds_long", 1, 64, 160, 4, 600, 1, 3, (1, 1), "walk"), 0.5),
         (synth.Layer("rounds_short", 1, 64, 160, 4, 300, 1, 5, (2, 2), "walk"), 0.5),
@@ -270,10 +269,11 @@ def test_2d_fast_grids(torch):
 
 def test_wgrad_paths(torch):
     """Each route of the weight-gradient inverse DFT: one pass over all bins
-    for wide layers (taps padded to 16 or exact), bin slices whose weights fill
-    the LDS cap (8 x 8 taps), channel-tiled slices for more than 256 output
-    channels, a single slice written without partial sums, and 16 x 16
-    channel tiles over all bins (2 and 4 groups per tile, ragged tiles)."""
+    for wide layers (3 x 3 taps), the matrix product of filters of more than 9
+    taps (4 x 4, 8 x 8, ragged channel counts) and of small banks with few bins,
+    channel-tiled slices for more than 256 output channels (and a single one,
+    written without partial sums), and 16 x 16 channel tiles over all bins (2 and
+    4 groups per tile, ragged tiles)."""
     cases = [
         synth.Layer("wg_wide_k3", 2, 2, 128, 128, 8, 8, 3, (1, 1, 1, 1), "blur"),
         synth.Layer("wg_wide_k4", 2, 2, 128, 128, 8, 8, 4, (2, 1, 2, 1), "blur"),
@@ -282,6 +282,8 @@ def test_wgrad_paths(torch):
         synth.Layer("wg_single_slice", 1, 2, 4, 300, 20, 1, 3, (1, 1), "walk"),
         synth.Layer("wg_tile_ng2", 2, 2, 256, 256, 8, 8, 3, (1, 1, 1, 1), "blur"),
         synth.Layer("wg_tile_ng4_ragged", 2, 2, 200, 260, 6, 6, 4, (2, 1, 2, 1), "blur"),
+        synth.Layer("wg_tile_ng4_ragged_k3", 2, 2, 200, 260, 6, 6, 3, (1, 1, 1, 1), "blur"),
+        synth.Layer("wg_single_slice_f300", 1, 2, 64, 300, 20, 1, 3, (1, 1), "walk"),
     ]
     for i, layer in enumerate(cases):
         for c in (0.0, 0.5):
@@ -301,8 +303,8 @@ def test_wgrad_paths(torch):
 def test_contraction_shapes(torch):
     """The tiled contraction at edge shapes: ragged tiles in m, n and k; a
     single bin with 2048 input channels (k split over many partial tiles,
-    summed in a fixed order); few bins with long k; an odd channel count (the
-    operands' 16-byte pairs do not align: the generic path); a 1-D layer.
+    summed in a fixed order); few bins with long k; an odd channel count (one
+    element per load along k); a 1-D layer.
     Each twice in a row on one workspace: results equal run to run."""
     cases = [
         (synth.Layer("ragged", 2, 70, 66, 130, 6, 6, 3, (1, 1, 1, 1), "blur"), 0.0),
@@ -339,19 +341,15 @@ def test_contraction_shapes(torch):
 
 def test_combined_backward(torch):
     """bl_conv_backward (both gradients from one DY spectrum; the two
-    contractions in one launch where they share a tile shape, the pass with
-    the longer sum split along k into partial spectra that the inverse
-    transforms add) against the oracle, equal run to run and with or without
-    reuse flags, and within rounding of the separate backward calls.  The
-    ResNet stack at c = 0.5 covers the 64-channel layer (grad-weight split in
-    two, its partials added as more bin slices), the 128-channel layer (no
-    split), the 256-channel layer (different tiles: two launches) and the
-    512-channel layer (grad-input split in four, added by the 2-D inverse as
-    it loads); the 64-channel layer at c = 0 and 0.75 (grad-weight partials
-    summed by the one-pass inverse DFT as it loads them); then a ragged layer,
-    a 1-D layer (grad-input partials summed before the chirp-z inverse), a
-    layer whose grad-weight partials the one-pass inverse DFT sums beside the
-    2-D inverse, and a bfloat16 plan."""
+    contractions in one launch, the input gradient's split along k into partial
+    spectra that the inverse transforms add where the tiles are few) against
+    the oracle, equal run to run and with or without reuse flags, and within
+    rounding of the separate backward calls.  The ResNet stack at c = 0.5 covers
+    the 64-channel layer (the weight gradient's inverse as a product), the 128-
+    and 256-channel layers and the 512-channel layer (grad-input split in four,
+    added by the 2-D inverse as it loads); the 64-channel layer at c = 0 and
+    0.75; then a ragged layer, a 1-D layer, a layer whose weight gradient has
+    the longer sums, and a bfloat16 plan."""
     # (layer, rate, plan flags, workload (config, layer) or None for random inputs)
     cases = [(synth.WORKLOADS[3].layers[i], 0.5, 0, (3, i)) for i in range(4)]
     cases += [(synth.WORKLOADS[3].layers[0], c, 0, (3, 0)) for c in (0.0, 0.75)]
@@ -406,8 +404,8 @@ def test_combined_backward_random_medium(torch):
     batch counts reach the tiled contractions (multiples of the tile sizes and
     ragged counts, up to about 600 channels), so that the plan's choices of
     tile shape, pairing of the two backward contractions and k splits (partial
-    spectra added by the inverses or the weight-gradient slices) vary from case
-    to case; 2-D and 1-D, against the oracle and the separate backward calls."""
+    spectra added by the inverses) vary from case to case; 2-D and 1-D, against
+    the oracle and the separate backward calls."""
     rng = np.random.default_rng(3100)
     chans = [16, 32, 48, 64, 96, 128, 160, 192, 256, 320, 384, 512, 17, 33, 70, 130, 200, 260, 513, 600]
     dev = torch.device("cuda:0")
@@ -457,9 +455,10 @@ def test_combined_backward_random_medium(torch):
 
 def test_thin_contractions(torch):
     """Layers where a contraction size (batch, input or output channels) is at
-    most 8, which run the memory-bound vector-ALU contraction: lanes over
-    output columns with k split over a block's waves or not, strided and
-    contiguous operands, and one output row per wave with a cross-lane sum."""
+    most 8, on both sides of the bounds between the memory-bound vector-ALU
+    contraction (lanes over output columns with k split over a block's waves or
+    not, strided and contiguous operands, and one output row per wave with a
+    cross-lane sum) and mostly empty matrix tiles."""
     cases = [
         synth.Layer("thin_c1_1d", 1, 64, 1, 128, 200, 1, 8, (3, 4), "walk"),
         synth.Layer("thin_c3_2d", 2, 4, 3, 64, 12, 12, 3, (1, 1, 1, 1), "blur"),
@@ -491,8 +490,8 @@ BF16_EXACT_TOL = 1e-2
 def test_bf16_contraction_parity(torch):
     """Plans with BL_DESC_BF16_SPECTRA against the oracle whose channel
     contraction rounds both operands to bfloat16 (round to nearest even) and
-    sums exactly: the MFMA tiles (with and without split k), the thin
-    vector-ALU contraction and the generic one, 1-D and 2-D."""
+    sums exactly: the MFMA tiles (whole and ragged) and the thin vector-ALU
+    contraction, 1-D and 2-D."""
     cases = [
         synth.Layer("bf_tiled_2d", 2, 16, 32, 48, 12, 12, 3, (1, 1, 1, 1), "blur"),
         synth.Layer("bf_tiled_1d", 1, 32, 16, 24, 200, 1, 8, (3, 4), "walk"),
@@ -545,8 +544,8 @@ def _check_bf16_words(words, ref):
 def test_bf16_stored_spectra_and_energy(torch):
     """With BL_DESC_BF16_SPECTRA the spectra X, W and DY are stored as
     bfloat16 pairs: every forward-transform path (2-D radix 2 x odd grids,
-    1-D chirp-z over 1024 points with one or two series per transform and over
-    256/512 points, the direct DFT on odd grids, the filter transform) against
+    1-D chirp-z over 1024 points with one or two series per transform, the matrix
+    products of short series and of an odd grid, the filter transform) against
     the oracle's spectra rounded to bfloat16, and the per-bin input energies of
     the stored spectrum against the oracle's energies of the rounded one."""
     dev = torch.device("cuda:0")
@@ -782,8 +781,8 @@ def test_graph_replays_match_eager(torch):
     """A layer's three passes captured in a HIP graph and replayed several times,
     with other eager library work, a poisoned workspace and outputs, and
     synchronisations between the replays: every replay's outputs are
-    bit-identical to the eager calls' (1-D chirp-z, 2-D, thin and tiled
-    contractions, bfloat16 spectra, the fused small-map forward)."""
+    bit-identical to the eager calls' (1-D by products and chirp-z, 2-D, thin and
+    tiled contractions, bfloat16 spectra, the fused small-map forward)."""
     dev = torch.device("cuda:0")
     cases = [
         (synth.Layer("graph_1d", 1, 16, 24, 40, 300, 1, 5, (2, 2), "walk"), 0.5, 0),
@@ -791,6 +790,7 @@ def test_graph_replays_match_eager(torch):
         (synth.Layer("graph_thin", 1, 8, 1, 64, 200, 1, 8, (3, 4), "walk"), 0.0, 0),
         (synth.Layer("graph_bf16", 2, 16, 32, 48, 12, 12, 3, (1, 1, 1, 1), "blur"), 0.25, blconv.BL_DESC_BF16_SPECTRA),
         (synth.Layer("graph_fused", 2, 4, 8, 6, 8, 8, 3, (1, 1, 1, 1), "blur"), 0.0, blconv.BL_DESC_FUSED_FORWARD),
+        (synth.Layer("graph_chirp", 1, 25, 125, 127, 515, 1, 3, (1, 1), "walk"), 0.5, 0),
     ]
     other = synth.Layer("graph_other", 2, 2, 8, 8, 10, 10, 3, (1, 1, 1, 1), "blur")
     ox, ow, ody = synth.random_inputs(other, 5)
