@@ -42,6 +42,8 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0      # MI355X HBM3E, GB/s
 MFMA_F32_PEAK_TF = 157.3   # MI355X dense fp32 matrix, TFLOP/s
+# six bf16 products to one of split fp32 operands (csrc/split.hpp), at the dense bf16 matrix rate of 2.5 PFLOP/s
+SPLIT_CEILING_TF = 2500.0 / 6
 RIDGE = MFMA_F32_PEAK_TF * 1e12 / (HBM_PEAK_GBS * 1e9)
 
 
@@ -217,7 +219,10 @@ def roofline(agg):
             "unit": "TFLOP/s", "frac": nf / s / 1e12 / MFMA_F32_PEAK_TF, "traffic": None,
             "avg_launch_us": 1e3 * ms / n, "launches": n, "per_launch_flops": nf / n,
             "per_launch_bytes": nb / n, "hbm_GBps": nb / s / 1e9,
-            "flop_count": "algorithmic: 8 real flops per complex multiply-add"}
+            "flop_count": "algorithmic: 8 real flops per complex multiply-add",
+            "kernel_ceiling": SPLIT_CEILING_TF, "frac_of_kernel_ceiling": nf / s / 1e12 / SPLIT_CEILING_TF,
+            "kernel_ceiling_note": "dense bf16 matrix rate / 6: fp32 products run as six bf16 ones of split operands; "
+                                   "peak is the fp32 matrix rate, which such a kernel can pass"}
 
 
 KERNEL_SOURCES = {"spec_fwd_1d": "bluestein.hip", "spec_inv_1d": "bluestein.hip", "spec_fwd_2d": "fft2d.hip",

@@ -46,28 +46,37 @@
  *
  * Ownership: the caller owns every device buffer (x, w, y, dy, dx, dw and the
  * workspace ws).  Creating and querying a plan makes no HIP call.  The plan
- * also owns device tables, built in double precision on the host or the device: the operands of transforms that run as
- * matrix products (2-D grids without their own FFT kernels: 12 bytes per kept
- * column and input column, and per kept row and input row; series and small
- * planes: 12 bytes per kept bin and sample of a plane, at most 64 MiB a
- * table), those of the chirp-z 1-D transforms (under 100 KB), the roots of
- * unity of the filter DFT (8 (L_h + L_w) bytes) and the inverse-DFT weights of
- * the weight gradient (8 to 12 bytes per kept bin and filter tap).  The first
- * compute call of the plan that needs a table on a device builds it there; that call
- * allocates and synchronises, so make each kind of call once outside
- * stream capture before capturing it (a captured call that finds a transform's
- * table missing takes a slower path without it; one that finds the weight
- * gradient's missing returns BL_ERR_UNSUPPORTED).  Where memory for a product's table is
- * short, the transform takes a path without it.  Every other compute call allocates nothing,
- * makes no host synchronisation and enqueues its kernels on `stream` (a
- * hipStream_t, passed as void*; NULL = the default stream).
+ * also owns device tables, made in double precision on the host or the device:
+ * the operands of transforms that run as matrix products (2-D grids without
+ * their own FFT kernels: 12 bytes per kept column and input column, and per kept
+ * row and input row; series and small planes: 6 bytes per kept bin and sample of
+ * a plane, at most 64 MiB a table), those of the chirp-z 1-D transforms (under
+ * 100 KB), the roots of unity of the filter DFT (8 (L_h + L_w) bytes) and the
+ * inverse-DFT weights of the weight gradient (6 to 8 bytes per kept bin and
+ * filter tap).  The first compute call of the plan that needs a table on a
+ * device makes it there; that call allocates and synchronises, so make each kind
+ * of call once outside stream capture before capturing it (a captured call that
+ * finds a transform's table missing takes a slower path without it; one that
+ * finds the weight gradient's missing returns BL_ERR_OOM).  Where memory for a
+ * product's table is short, the transform takes a path without it.  Every other
+ * compute call allocates nothing, makes no host synchronisation and enqueues its
+ * kernels on `stream` (a hipStream_t, passed as void*; NULL = the default stream).
  * bl_conv_plan_destroy frees the tables (no kernel of the plan may still be
  * running).
  *
  * Errors: every call returns a bl_status_t.  Arguments are validated on the host
  * before anything is enqueued; a call that returns an error has enqueued no
- * kernel, except BL_ERR_HIP, which reports a failed launch (work enqueued before
- * it by the same call may have run).
+ * kernel, except BL_ERR_HIP, which reports a failed launch, and BL_ERR_OOM of a
+ * compute call, which reports a table that could not be made (work enqueued
+ * before either by the same call may have run).
+ *
+ * Range: fp32 values are multiplied on the bf16 matrix cores as sums of three
+ * bfloat16 parts.  All 24 significant bits enter from 2^-110 (7.7e-34) in
+ * magnitude on; below that the last part is subnormal and bits under 2^-134 are
+ * lost, so tensors whose values or spectra are all smaller should be scaled up.
+ * A sample, filter tap or spectrum value of 3.3962e38 (0.2 % below float's
+ * largest, where bfloat16 rounds to infinity) or more gives NaN, as infinities
+ * and NaN do, in every result that it enters.
  *
  * Threading: a plan's geometry is immutable after creation (the device tables
  * are built under a lock); calls with distinct workspaces may run

@@ -42,8 +42,8 @@ hipEvent_t prof_event(int slot, int end) { return g_prof.ev[2 * slot + end]; }
 //    samples, c = 0.5: 2048 series 5.0 / 4.7 against 11.9 / 11.6, 16384 14.6 / 16.2
 //    against 26.1 / 23.2), and until its multiply-adds fill the chip the one of 1024 (512 samples, c = 0.5: 2048 series 9.6 / 8.7
 //    against 11.0 / 10.6, 4096 14.9 / 10.7 against 12.5 / 12.7, 8192 21.3 / 18.7
-//    against 15.0 / 15.8).  Past about 700 samples only the direct sum is left:
-//    1000 samples, 2048 series 468 / 603.
+//    against 15.0 / 15.8).  Past about 700 samples its alternative is the direct
+//    sum: 1000 samples, 2048 series 468 / 603.
 //  - planes on grids without FFT kernels: one product while its table is small
 //    or the planes few, else two (mdft.hip).  10 x 10, c = 0, 8192 planes 8.0 /
 //    5.6 against 10.4 / 10.0; 14 x 14 13.5 / 10.2 against 15.3 / 12.5; 20 x 20, 512

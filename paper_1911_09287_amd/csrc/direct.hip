@@ -1,5 +1,6 @@
 // Direct (pruned DFT) transforms, filter spectrum, weight-gradient inverse
-// DFT and the per-bin channel contraction on fp32 MFMA (gfx950).
+// DFT and the per-bin channel contraction on fp32 MFMA of matrices past 2 GB
+// (gfx950).
 //
 //   spec_fwd_direct  zero-pad + real 2-D DFT + band mask of real planes (x or
 //                    dy): a row pass that emits only kept columns v <= r_w, then

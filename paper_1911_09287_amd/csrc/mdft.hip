@@ -578,13 +578,12 @@ bl_status_t launch_mdft_inv(const bl_conv_plan_s* p, const float2* in, float* ou
   MdftSetup f;
   const bl_status_t st = mdft_inv_setup(p, P, OH, OW, ci, cj, nsplit, pstride, f, s);
   if (st != BL_OK) return st;
-#define X(a, b)                                                                                                  \
-  if (f.ka == a && f.kb == b)                                                                                    \
-    return f.g.nsplit > 1 ? mdft_go(k_mdft_inv<a, b, true>, "spec_inv_2d", f.blocks, f.lds, f.bytes, f.flops, s, in, \
-                                    out, f.g)                                                                    \
-                          : mdft_go(k_mdft_inv<a, b, false>, "spec_inv_2d", f.blocks, f.lds, f.bytes, f.flops, s, in, \
-                                    out, f.g);
-  X(1, 1) X(1, 2) X(1, 4) X(2, 1) X(2, 2) X(2, 4)
+#define X(a, b, parts)                                 \
+  if (f.ka == a && f.kb == b && parts == (f.g.nsplit > 1)) \
+    return mdft_go(k_mdft_inv<a, b, parts>, "spec_inv_2d", f.blocks, f.lds, f.bytes, f.flops, s, in, out, f.g);
+  X(1, 1, false) X(1, 2, false) X(1, 4, false) X(2, 1, false) X(2, 2, false) X(2, 4, false)
+  // (more than 32 row frequencies by 16 columns are at least 1088 bins: too many for a contraction to be split)
+  X(1, 1, true) X(1, 2, true) X(1, 4, true) X(2, 1, true)
 #undef X
   return BL_ERR_UNSUPPORTED;
 }

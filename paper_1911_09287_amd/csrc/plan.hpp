@@ -112,9 +112,9 @@ struct bl_conv_plan_s {
   // output inverse adds (1: not split), for launches of few tiles
   int fwd_split, fwd_ks;  // (fwd_ks: wave groups per tile, as BlContractTiling::ks)
   size_t off_X, off_W, off_DY, off_T, off_DW, off_Part, off_CPart, ws_bytes;
-  // small device tables (1-D chirps and filter spectra, weight-gradient
-  // inverse-DFT weights), built on a plan's first call that needs them on
-  // each device; freed with the plan
+  // device tables (operands of the matrix-product transforms, 1-D chirps and
+  // filter spectra, weight-gradient inverse-DFT weights), made in a plan's first
+  // call that needs them on each device; freed with the plan
   mutable void* tables;
 };
 

@@ -1,5 +1,7 @@
 // fp32 products on the bf16 matrix cores: exact splitting of floats into three
-// bfloat16 parts, shared by the channel contraction and the matrix transforms.
+// bfloat16 parts, shared by the channel contraction and the matrix transforms
+// (after Henry, Tang and Heinecke, "Leveraging the bfloat16 Artificial
+// Intelligence Datatype For Higher-Precision Computations", ARITH 2019).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -19,7 +21,11 @@ typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 // Two floats as three bfloat16 pairs (first value in the low half) whose sum
 // is exact: x1 = bf16(x), x2 = bf16(x - x1), x3 = bf16(x - x1 - x2); the
 // differences are exact, and what the third part rounds is below the first's
-// 24th bit.
+// 24th bit.  (From 2^-110 on: smaller values' last part is subnormal and ends at
+// 2^-133.  From 3.3962e38 on, 0.2 % below float's largest, the first part rounds
+// to infinity and the third is NaN; clamping it there costs an instruction per
+// value, 1 to 2 % of most passes: 512 channels 116.9 -> 119.4 us, a series of
+// 1250 samples 39.5 -> 40.4.)
 __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
   return __builtin_bit_cast(unsigned, __builtin_convertvector((floatx2){a, b}, bf16x2));
 }

@@ -40,7 +40,8 @@ LIBRARY_NAMES = OrderedDict([
     ("wgrad_idft", r"k_wgrad_wide<|k_wgrad_idft<|k_wgrad_tile<"),
     ("wgrad_reduce", r"k_wgrad_reduce"),
     # launched under the transforms' names, or the weight gradient's inverse DFT
-    ("matrix transforms", r"k_mdft_|k_pgemm<"),
+    ("matrix transforms", r"k_mdft_(fwd|inv)<|k_pgemm<"),
+    ("plan tables", r"k_(mdft|pgemm)_table<"),
 ])
 MARKER = "spin_kernel"
 

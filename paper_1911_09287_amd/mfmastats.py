@@ -2,8 +2,9 @@
 
 Measurement tool (not used by the library).  Inputs:
 
-* the ``*_counter_collection.csv`` of ``rocprofv3 --pmc MfmaFlopsF32 MfmaUtil``
-  run on ``bench.py`` (every dispatch of the run; all at one compression rate);
+* the ``*_counter_collection.csv`` of ``rocprofv3 --pmc MfmaFlopsF32 MfmaFlopsBF16
+  MfmaUtil`` run on ``bench.py`` (every dispatch of the run; all at one
+  compression rate);
 * the ``*_kernel_trace.csv`` of a plain ``rocprofv3 --kernel-trace`` run of the
   benchmark's headline command: the kernel durations are taken from there,
   between the first two marker dispatches (the timed steps), because a counter
@@ -12,9 +13,9 @@ Measurement tool (not used by the library).  Inputs:
   (8 real flops per complex multiply-add over the kept bins).
 
 For each contraction pass (library kernel name) it prints the dispatches, the
-executed matrix-core flops per dispatch (``MfmaFlopsF32`` = 512 x
-``SQ_INSTS_VALU_MFMA_MOPS_F32``), their ratio to the algorithmic flops (tile
-padding), ``MfmaUtil`` (matrix-core busy cycles over active GPU cycles times
+executed matrix-core flops per dispatch (``MfmaFlopsF32`` and ``MfmaFlopsBF16``,
+512 x ``SQ_INSTS_VALU_MFMA_MOPS_F32`` or ``_BF16``), their ratio to the
+algorithmic flops (six products of an fp32 one, and tile padding), ``MfmaUtil`` (matrix-core busy cycles over active GPU cycles times
 SIMDs, in percent, as rocprofv3 derives it), the average duration, and the
 executed and algorithmic rates as fractions of the fp32 matrix-core peak.
 
@@ -40,6 +41,11 @@ def counters(path):
         d = out.setdefault(r["Dispatch_Id"], (r["Kernel_Name"], {}))
         d[1][r["Counter_Name"]] = d[1].get(r["Counter_Name"], 0.0) + float(r["Counter_Value"])
     return out
+
+
+def flops(c):
+    """Matrix-core flops of a dispatch's counters."""
+    return c.get("MfmaFlopsF32", 0.0) + c.get("MfmaFlopsBF16", 0.0)
 
 
 def durations(path):
@@ -76,7 +82,7 @@ def main():
         ds = [t for s, t in dur if re.search(pat, s)]
         if not cs or not ds:
             continue
-        fl = sum(c.get("MfmaFlopsF32", 0.0) for c in cs) / len(cs)
+        fl = sum(flops(c) for c in cs) / len(cs)
         ut = sum(c.get("MfmaUtil", 0.0) for c in cs) / len(cs)
         us = sum(ds) / len(ds)
         ex_tf = fl / (us * 1e-6) / 1e12
@@ -90,10 +96,10 @@ def main():
     print("|---|---|---|---|")
     per = defaultdict(list)
     for s, c in cnt.values():
-        if "MfmaFlopsF32" in c and c["MfmaFlopsF32"] > 0:
+        if flops(c) > 0:
             per[short(s)].append(c)
     for s, cs in sorted(per.items()):
-        print(f"| {s} | {len(cs)} | {sum(c['MfmaFlopsF32'] for c in cs) / len(cs) / 1e9:.3f} | "
+        print(f"| {s} | {len(cs)} | {sum(flops(c) for c in cs) / len(cs) / 1e9:.3f} | "
               f"{sum(c.get('MfmaUtil', 0.0) for c in cs) / len(cs):.1f} |")
 
 

@@ -62,6 +62,7 @@ def test_kernel_table_and_roofline():
     assert r["kernel"] == "contract_bwd" and r["bound"] == "mfma" and r["unit"] == "TFLOP/s"
     assert r["achieved"] == pytest.approx(2.88e9 / 30e-6 / 1e12)
     assert r["frac"] == pytest.approx(r["achieved"] / 157.3)
+    assert r["frac_of_kernel_ceiling"] == pytest.approx(r["achieved"] * 6 / 2500.0)
     assert r["per_launch_flops"] == pytest.approx(2.88e9) and r["avg_launch_us"] == pytest.approx(30.0)
 
 
