@@ -141,6 +141,7 @@ extern "C" bl_status_t bl_conv_forward(bl_conv_plan_t p, const float* x, const f
   if (flags & ~(BL_REUSE_X | BL_REUSE_W)) return BL_ERR_INVALID_ARG;
   if ((!(flags & BL_REUSE_X) && !x) || (!(flags & BL_REUSE_W) && !w)) return BL_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  const TableScope tables;
   void* X = spec_at(ws, p->off_X);
   void* Wf = spec_at(ws, p->off_W);
   float2* T = ws_at(ws, p->off_T);
@@ -179,6 +180,7 @@ extern "C" bl_status_t bl_conv_backward_input(bl_conv_plan_t p, const float* dy,
   if (flags & ~BL_REUSE_W) return BL_ERR_INVALID_ARG;
   if (!(flags & BL_REUSE_W) && !w) return BL_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  const TableScope tables;
   void* Wf = spec_at(ws, p->off_W);
   void* DY = spec_at(ws, p->off_DY);
   float2* T = ws_at(ws, p->off_T);
@@ -194,6 +196,7 @@ extern "C" bl_status_t bl_conv_backward_weight(bl_conv_plan_t p, const float* x,
   if (flags & ~(BL_REUSE_X | BL_REUSE_DY)) return BL_ERR_INVALID_ARG;
   if ((!(flags & BL_REUSE_X) && !x) || (!(flags & BL_REUSE_DY) && !dy)) return BL_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  const TableScope tables;
   void* X = spec_at(ws, p->off_X);
   void* DY = spec_at(ws, p->off_DY);
   float2* DW = ws_at(ws, p->off_DW);
@@ -212,6 +215,7 @@ extern "C" bl_status_t bl_conv_backward(bl_conv_plan_t p, const float* dy, const
   if ((!(flags & BL_REUSE_DY) && !dy) || (!(flags & BL_REUSE_W) && !w) || (!(flags & BL_REUSE_X) && !x))
     return BL_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  const TableScope tables;
   void* X = spec_at(ws, p->off_X);
   void* Wf = spec_at(ws, p->off_W);
   void* DY = spec_at(ws, p->off_DY);

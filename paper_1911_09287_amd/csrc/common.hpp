@@ -83,11 +83,24 @@ __device__ inline int kept_row_d(int r, int r_h, int Lh, int R) { return r <= r_
 bl_status_t plan_table(const bl_conv_plan_s* p, const std::vector<long>& key,
                        const std::function<void(std::vector<float2>&)>& build, const float2** out, hipStream_t s);
 // The same for a table of n float2 that `fill` makes by a kernel on stream s.
-// Nothing is built on the host or copied: what a new plan's first pass takes
-// with tables made by the host / by a kernel is 214 / 119 us on a grid of 59 x
-// 59 points (one image, forward), 333 / 211 on 32 x 25 (training step).
+// Nothing is built on the host or copied, and a call waits once for all of its
+// tables: what a new plan's first pass takes with tables made by the host / by
+// kernels is 214 / 116 us on a grid of 59 x 59 points (one image, forward), 333 /
+// 187 on 32 x 25 and 187 / 110 for 3 -> 16 channels on 34 x 34 (training steps).
 bl_status_t plan_table_on_device(const bl_conv_plan_s* p, const std::vector<long>& key, size_t n,
                                  const std::function<void(float2*)>& fill, const float2** out, hipStream_t s);
+// Held by a compute call: what its kernels make is waited for once, when it
+// returns (the call's own stream reads it in order), and by any other thread
+// that finds it sooner.  Without one, each table is waited for where it is made.
+struct TableScope {
+  hipEvent_t made = nullptr;  // after the last table's kernel
+  void* cache = nullptr;      // the plan's tables
+  bool pending = false;       // a kernel recorded, its table not entered yet
+  TableScope();
+  ~TableScope();
+  TableScope(const TableScope&) = delete;
+  TableScope& operator=(const TableScope&) = delete;
+};
 long float_key(float x);  // bit pattern of x, for keys
 // Allows kernel `kern` up to `bytes` of dynamic LDS on the current device
 // (hipFuncAttributeMaxDynamicSharedMemorySize), once per kernel and device.

@@ -327,24 +327,23 @@ __global__ __launch_bounds__(256 * NG) void k_wgrad_tile(const float2* __restric
   }
 }
 
-// Inverse-DFT weights E[bin][t] of the weight gradient, in double precision.
-void host_wgrad_weights(const bl_conv_plan_s* p, std::vector<float2>& out) {
-  const int T = p->Kh * p->Kw, B = (int)p->kept;
-  const long LL = (long)p->Lh * p->Lw;
-  const int nyq = (p->Lw % 2 == 0) ? p->Lw / 2 : -1;
-  const double pi = 3.141592653589793238462643383279502884;
-  out.assign((size_t)B * T, make_float2(0.f, 0.f));
-  for (int bin = 0; bin < B; ++bin) {
-    const int r = bin / p->V, v = bin % p->V;
-    const int u = bl_kept_row(r, p->r_h, p->Lh, p->R);
-    const double h = ((v == 0 || v == nyq) ? 1.0 : 2.0) / (double)LL;
-    for (int t = 0; t < T; ++t) {
-      const int ta = t / p->Kw, tb = t % p->Kw;
-      const long idx = ((long)u * ta * p->Lw + (long)v * tb * p->Lh) % LL;
-      const double ang = 2.0 * pi * (double)idx / (double)LL;
-      out[(size_t)bin * T + t] = make_float2((float)(h * std::cos(ang)), (float)(h * std::sin(ang)));
-    }
-  }
+// Inverse-DFT weights E[bin][t] of the weight gradient (n of them), in double precision.
+__global__ __launch_bounds__(kThreads) void k_wgrad_table(float2* __restrict__ out, WgradGeom g, int n) {
+  const int id = blockIdx.x * kThreads + threadIdx.x;
+  if (id >= n) return;
+  const int bin = id / g.T, t = id - bin * g.T, v = bin % g.V, u = kept_row_d(bin / g.V, g.r_h, g.Lh, g.R);
+  const long LL = (long)g.Lh * g.Lw;
+  const long turn = ((long)u * (t / g.Kw) * g.Lw + (long)v * (t % g.Kw) * g.Lh) % LL;
+  const double h = (v == 0 || 2 * v == g.Lw ? 1.0 : 2.0) / (double)LL;
+  double c, s;
+  sincospi(2.0 * (double)turn / (double)LL, &s, &c);
+  out[id] = make_float2((float)(h * c), (float)(h * s));
+}
+
+// e^{-2 pi i k / Lh} (k < Lh), then e^{-2 pi i k / Lw} (k < Lw).
+__global__ __launch_bounds__(kThreads) void k_filt_roots(float2* __restrict__ out, int Lh, int Lw) {
+  const int k = blockIdx.x * kThreads + threadIdx.x;
+  if (k < Lh + Lw) out[k] = k < Lh ? unit_root(k, Lh, -1.0) : unit_root(k - Lh, Lw, -1.0);
 }
 
 // ---------------------------------------------------------------------------
@@ -512,18 +511,6 @@ bl_status_t launch_spec_inv_direct(const bl_conv_plan_s* p, const float2* in, fl
   });
 }
 
-
-// e^{-2 pi i k / Lh} for k < Lh, then e^{-2 pi i k / Lw} for k < Lw, in double precision.
-void host_filt_roots(const bl_conv_plan_s* p, std::vector<float2>& out) {
-  const double pi = 3.141592653589793238462643383279502884;
-  out.clear();
-  for (int L : {p->Lh, p->Lw})
-    for (int k = 0; k < L; ++k) {
-      const double a = 2.0 * pi * (double)k / (double)L;
-      out.push_back(make_float2((float)std::cos(a), (float)(-std::sin(a))));
-    }
-}
-
 bl_status_t filt_setup(const bl_conv_plan_s* p, bool use_table, FiltGeom& g, const float2** roots, long* blocks,
                        size_t* lds, double* bytes, hipStream_t s) {
   g = FiltGeom{p->Cout, p->Cin, p->Kh, p->Kw, p->Lh, p->Lw, p->r_h, p->R, p->V, 0, 0};
@@ -547,7 +534,14 @@ bl_status_t filt_setup(const bl_conv_plan_s* p, bool use_table, FiltGeom& g, con
   *bytes = (double)CF * p->Kh * p->Kw * 4 + (double)CF * B * (p->bf16 ? 4 : 8);
   if (use_table) {
     const std::vector<long> key{3, p->Lh, p->Lw};
-    const bl_status_t st = plan_table(p, key, [&](std::vector<float2>& h) { host_filt_roots(p, h); }, roots, s);
+    const int n = p->Lh + p->Lw;
+    const bl_status_t st = plan_table_on_device(
+        p, key, n,
+        [&](float2* d) {
+          hipLaunchKernelGGL(k_filt_roots, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, d, p->Lh,
+                             p->Lw);
+        },
+        roots, s);
     return st == BL_ERR_UNSUPPORTED ? BL_OK : st;
   }
   return BL_OK;
@@ -586,7 +580,14 @@ bool wgrad_wide(const bl_conv_plan_s* p) {
 
 bl_status_t wgrad_table(const bl_conv_plan_s* p, const float2** Et, hipStream_t s) {
   const std::vector<long> key{2, p->Lh, p->Lw, p->r_h, p->R, p->V, p->Kh, p->Kw};
-  return plan_table(p, key, [&](std::vector<float2>& h) { host_wgrad_weights(p, h); }, Et, s);
+  const int n = (int)p->kept * p->Kh * p->Kw;
+  return plan_table_on_device(
+      p, key, n,
+      [&](float2* d) {
+        const WgradGeom g{p->Cout, p->Cin, p->Kh, p->Kw, p->Kh * p->Kw, p->Lh, p->Lw, p->r_h, p->R, p->V, 0, 0, 0};
+        hipLaunchKernelGGL(k_wgrad_table, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, s, d, g, n);
+      },
+      Et, s);
 }
 
 bool wgrad_sliced_setup(const bl_conv_plan_s* p, WgradGeom& g, long* xblocks, int* slices, size_t* lds,

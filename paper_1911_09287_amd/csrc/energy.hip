@@ -68,6 +68,7 @@ extern "C" bl_status_t bl_conv_input_energy(bl_conv_plan_t p, const float* x, vo
   if (!(flags & BL_REUSE_X) && !x) return BL_ERR_INVALID_ARG;
   if (p->kept > 2147483647L) return BL_ERR_UNSUPPORTED;
   hipStream_t s = static_cast<hipStream_t>(stream);
+  const TableScope tables;
   void* X = static_cast<char*>(ws) + p->off_X;
   const long P = (long)p->N * p->Cin;
   if (!(flags & BL_REUSE_X)) {

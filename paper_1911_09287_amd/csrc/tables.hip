@@ -19,12 +19,16 @@ struct TabEntry {
   int dev;
   std::vector<long> key;
   float2* d;
+  const TableScope* making;  // the call whose kernel makes it, until that has been waited for
 };
 std::mutex g_tab_mu;
+thread_local TableScope* t_scope = nullptr;
 
-}  // namespace
-
-namespace {
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &c) != hipSuccess) (void)hipGetLastError();
+  return c != hipStreamCaptureStatusNone;
+}
 
 // The table of `key` on the current device, made by `make` (which allocates
 // and fills it) where the plan has none yet.
@@ -38,21 +42,25 @@ bl_status_t find_or_make(const bl_conv_plan_s* p, const std::vector<long>& key, 
   if (!cache) return BL_ERR_OOM;
   for (const TabEntry& e : *cache)
     if (e.dev == dev && e.key == key) {
+      if (e.making && e.making != t_scope) {  // (under the lock: the scope is still there)
+        if (capturing(s)) return BL_ERR_UNSUPPORTED;
+        if (hipEventSynchronize(e.making->made) != hipSuccess) return BL_ERR_HIP;
+      }
       *out = e.d;
       return BL_OK;
     }
   // a stream that is being captured allows no allocation and no wait: the
   // caller takes a path without the table, if it has one
-  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &capture) != hipSuccess) (void)hipGetLastError();
-  if (capture != hipStreamCaptureStatusNone) return BL_ERR_UNSUPPORTED;
+  if (capturing(s)) return BL_ERR_UNSUPPORTED;
   float2* d = nullptr;
   const bl_status_t st = make(&d);
   if (st != BL_OK) {
     if (d) (void)hipFree(d);
     return st;
   }
-  cache->push_back(TabEntry{dev, key, d});
+  const bool waits = t_scope && t_scope->pending;  // for a kernel of this call
+  if (waits) t_scope->cache = cache, t_scope->pending = false;
+  cache->push_back(TabEntry{dev, key, d, waits ? t_scope : nullptr});
   *out = d;
   return BL_OK;
 }
@@ -84,9 +92,31 @@ bl_status_t plan_table_on_device(const bl_conv_plan_s* p, const std::vector<long
     const bl_status_t st = allocate(d, n);
     if (st != BL_OK) return st;
     fill(*d);
-    // (waited for: a call on another stream may be the next to read it)
-    return hipGetLastError() == hipSuccess && hipStreamSynchronize(s) == hipSuccess ? BL_OK : BL_ERR_HIP;
+    if (hipGetLastError() != hipSuccess) return BL_ERR_HIP;
+    // waited for: a call on another stream may be the next to read it
+    if (TableScope* t = t_scope) {
+      if (!t->made && hipEventCreateWithFlags(&t->made, hipEventDisableTiming) != hipSuccess) t->made = nullptr;
+      if (t->made && hipEventRecord(t->made, s) == hipSuccess) {
+        t->pending = true;
+        return BL_OK;
+      }
+      (void)hipGetLastError();
+    }
+    return hipStreamSynchronize(s) == hipSuccess ? BL_OK : BL_ERR_HIP;
   });
+}
+
+TableScope::TableScope() { t_scope = this; }
+
+TableScope::~TableScope() {
+  t_scope = nullptr;
+  if (!made) return;
+  (void)hipEventSynchronize(made);
+  std::lock_guard<std::mutex> lk(g_tab_mu);
+  if (cache)
+    for (TabEntry& e : *static_cast<std::vector<TabEntry>*>(cache))
+      if (e.making == this) e.making = nullptr;
+  (void)hipEventDestroy(made);
 }
 
 bl_status_t lds_opt_in(const void* kern, int bytes) {

@@ -41,7 +41,7 @@ LIBRARY_NAMES = OrderedDict([
     ("wgrad_reduce", r"k_wgrad_reduce"),
     # launched under the transforms' names, or the weight gradient's inverse DFT
     ("matrix transforms", r"k_mdft_(fwd|inv)<|k_pgemm<"),
-    ("plan tables", r"k_(mdft|pgemm)_table<"),
+    ("plan tables", r"k_(mdft|pgemm|wgrad)_table\b|k_filt_roots\b"),
 ])
 MARKER = "spin_kernel"
 

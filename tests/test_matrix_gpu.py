@@ -8,6 +8,7 @@ about 3e-7, so 1e-6 holds for every case while a dropped part of a split value
 (2^-9 to 2^-17 of it) does not.
 """
 import math
+import threading
 
 import pytest
 
@@ -333,6 +334,54 @@ def test_tables_are_held_once(torch):
     one = 6 * plan.kept * 2048  # three bfloat16 of a cosine and a sine for a bin and two samples
     say(f"[tables] {held / 1e6:.1f} MB held, {2 * one / 1e6:.1f} MB of two tables")
     assert held <= 2 * one + (8 << 20)  # (tiles, the other tables, and memory given out in blocks of 2 MB)
+
+
+@pytest.mark.parametrize("nd,sp,K", [(2, (28, 21), 5), (2, (32, 32), 3), (1, (270,), 8)])
+def test_first_calls_from_two_threads(torch, nd, sp, K):
+    """A new plan's first calls, from two threads on streams and workspaces of
+    their own: tables that one call makes are there for the other."""
+    lo, hi = (K - 1) // 2, K - 1 - (K - 1) // 2
+    layer = synth.Layer("threads", nd, 4, 24, 33, sp[0], sp[1] if nd == 2 else 1, K, (lo, hi) * nd, "blur")
+    dev = torch.device("cuda:0")
+    xt, wt, dyt = (torch.from_numpy(a).to(dev) for a in synth.random_inputs(layer, 4650))
+
+    def buffers(plan):
+        return plan.workspace(dev), torch.empty_like(dyt), torch.empty_like(xt), torch.empty_like(wt)
+
+    def step(plan, b, stream=None):
+        ws, y, dx, dw = b
+        plan.forward(xt, wt, y, ws, stream=stream)
+        plan.backward(dyt, None, None, dx, dw, ws, flags=blconv.BL_REUSE_X | blconv.BL_REUSE_W, stream=stream)
+
+    plan = blconv.plan_for_layer(layer, 0.5)
+    want = buffers(plan)
+    step(plan, want)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    for r in range(6):
+        plan = blconv.plan_for_layer(layer, 0.5)
+        got = [buffers(plan), buffers(plan)]
+        torch.cuda.synchronize()
+        together = threading.Barrier(2)
+        failed = []
+
+        def run(i):
+            together.wait()
+            try:
+                step(plan, got[i], streams[i])
+            except Exception as e:  # noqa: BLE001  -- reported below
+                failed.append(e)
+
+        threads = [threading.Thread(target=run, args=(i,)) for i in range(2)]
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        torch.cuda.synchronize()
+        assert not failed, failed
+        for b in got:
+            for a, e in zip(b[1:], want[1:]):
+                assert torch.equal(a, e), r
 
 
 @pytest.mark.parametrize("nd,sp,K", [(2, (28, 21), 5), (2, (9, 9), 3), (1, (270,), 8), (1, (512,), 5), (1, (900,), 3)])
