@@ -491,6 +491,7 @@ bl_status_t launch_contract_bwd_pair(const bl_conv_plan_s* p, const void* DY, co
   const bool few = p->N == 2 || (p->N == 1 && (p->kept <= 96 || (p->kept <= 640 && products <= 6000000)));
   if (!few && (contract_is_thin(p, Contract::GradInput) || contract_is_thin(p, Contract::GradWeight)))
     return BL_ERR_UNSUPPORTED;
+  if (p->bp_s1 == 0) return BL_ERR_UNSUPPORTED;
   CgemmArgs g1, g2;
   bool v1, v2;
   if (!tiled_args(p, Contract::GradInput, g1, v1) || !tiled_args(p, Contract::GradWeight, g2, v2)) return BL_ERR_UNSUPPORTED;

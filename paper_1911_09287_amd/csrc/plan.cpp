@@ -136,6 +136,15 @@ extern "C" bl_status_t bl_conv_plan_create(bl_conv_plan_t* out, const bl_conv_de
     const double load = (double)(tiles1 * st1 + tiles2 * st2) / 256.0;
     if (p->Lh > 1)
       while (p->bp_s1 < 4 && st1 % (2 * p->bp_s1) == 0 && st1 / p->bp_s1 >= 16 && 1.6 * st1 / p->bp_s1 > load) p->bp_s1 *= 2;
+    // A tile of the pair is one wave group's; where the longest is a serial chain
+    // well past the CUs' load, two launches whose groups share a tile's sum are
+    // the faster (combined call with stored spectra, pair / apart, us: 18 images,
+    // 17 -> 1000 channels, 6 bins 56.8 / 32.4; 4 images, 17 -> 496, 28 bins 33.7 /
+    // 22.9; -> 304 24.7 / 19.9, 12 stages apart, within the bound; 64 images, 64 ->
+    // 400, 76 bins 41.6 / 51.0).
+    const long longest = std::max((st1 + p->bp_s1 - 1) / p->bp_s1, st2);
+    const double apart = (double)st1 / p->ct[1].ks + (double)st2 / p->ct[2].ks;
+    if (longest - apart > 13 && longest > 2 * load) p->bp_s1 = 0;
   }
   // forward contractions with long sums in at most two tiles per CU are split
   // along k where the 2-D inverse can add the partial spectra as it loads them

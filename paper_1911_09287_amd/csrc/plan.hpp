@@ -105,7 +105,7 @@ struct bl_conv_plan_s {
   BlContractTiling ct[3];  // contraction tiling: forward, grad-input, grad-weight
   // paired backward contraction (one launch for grad-input and grad-weight):
   // k-splits of grad-input, whose partial sums (in the contraction-partials
-  // area) the inverse transform adds
+  // area) the inverse transform adds; 0: two launches
   int bp_s1;
   int bp_bm, bp_bn;  // the paired launch's tile shape
   // forward contraction split along k into partial spectra that the 2-D

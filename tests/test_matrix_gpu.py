@@ -290,6 +290,33 @@ def test_weight_gradient_by_product(torch, nd, N, ci, co, sp, K, c, product):
     assert max(errs) <= FP32_TOL, errs
 
 
+@pytest.mark.parametrize("N,ci,co,nd,sp,K,c,paired", [
+    (18, 17, 496, 2, (8, 8), 1, 0.75, False),   # 31 stages of grad-input against 1 tile's load
+    (4, 3, 340, 1, (60,), 3, 0.0, False),       # 22 stages, 6.5 apart
+    (4, 3, 272, 1, (60,), 3, 0.0, True),        # 17 stages, 5.3 apart
+    (18, 17, 512, 2, (8, 8), 1, 0.75, True),    # split in four: 8 stages
+    (64, 64, 400, 1, (300,), 3, 0.5, True),     # two groups a tile apart: 16.5 of 25 stages
+    (4, 17, 1000, 1, (700,), 3, 0.0, True),     # 63 stages within twice the load
+])
+def test_long_input_gradient_sums_run_apart(torch, N, ci, co, nd, sp, K, c, paired):
+    """A few tiles with long sums leave the paired backward launch; either way
+    against the oracle."""
+    p = (K - 1) // 2
+    layer = synth.Layer("long_sums", nd, N, ci, co, sp[0], sp[1] if nd == 2 else 1, K, (p, p) * nd, "blur")
+    plan = blconv.plan_for_layer(layer, c)
+    names = launches(torch, plan, "backward")
+    assert ("contract_bwd" in names) == paired and ("contract_dgrad" in names) != paired, (plan.kept, names)
+    x, w, dy = synth.random_inputs(layer, 4850 + co)
+    ws = plan.workspace(torch.device("cuda:0"))
+    xt, wt, dyt = (torch.from_numpy(a).to(ws.device) for a in (x, w, dy))
+    dx, dw = torch.full_like(xt, float("nan")), torch.full_like(wt, float("nan"))
+    plan.backward(dyt, wt, xt, dx, dw, ws)
+    torch.cuda.synchronize()
+    errs = [rel(g.cpu().numpy(), r) for g, r in zip((dx, dw), oracle_passes(layer, c, x, w, dy)[1:])]
+    say(f"[long sums] {ci}->{co} @{sp} {plan.kept} bins: {errs}")
+    assert max(errs) <= FP32_TOL, errs
+
+
 @pytest.mark.parametrize("N,ci,co,nd,sp,paired", [
     (1, 16, 16, 1, (1277,), True),      # 640 bins
     (1, 16, 16, 1, (1279,), False),     # 641 bins
