@@ -344,6 +344,34 @@ def test_one_image_pairs_few_products(torch, N, ci, co, nd, sp, paired):
     assert max(errs) <= FP32_TOL, errs
 
 
+@pytest.mark.parametrize("nd,N,ci,sp,K,c", [(2, 72, 64, (5, 5), 3, 0.75), (1, 32, 224, (1787,), 8, 0.0)])
+def test_energies_over_many_planes(torch, nd, N, ci, sp, K, c):
+    """Energies of spectra by one product: roundings of values average out over
+    the planes, those of a bin's table do not.  A phase rounded to 24 bits alone
+    gives 2^-25 on average; with its remainder only the operands' rounding is
+    left, averaged over the sample pairs."""
+    lo, hi = (K - 1) // 2, K - 1 - (K - 1) // 2
+    plan = blconv.Plan(nd, N, ci, 1, sp, K, (lo, hi) * nd, c)
+    dev = torch.device("cuda:0")
+    x = torch.randn(plan.x_shape(), device=dev, generator=torch.Generator(device=dev).manual_seed(4970))
+    got = plan.input_energy(x, plan.workspace(dev))
+    u, v = (torch.from_numpy(a).to(dev).double() for a in plan.bins())
+    lh, lw = plan.fft if nd == 2 else (1, plan.fft[0])
+    rows = x.double().reshape(N * ci, sp[0] if nd == 2 else 1, -1)
+    want = torch.zeros(plan.kept, dtype=torch.float64, device=dev)
+    i, j = torch.meshgrid(*(torch.arange(n, device=dev).double() for n in rows.shape[1:]), indexing="ij")
+    for at in range(0, plan.kept, 256):
+        b = slice(at, at + 256)
+        turns = u[b, None] * (i.reshape(1, -1) + (lo if nd == 2 else 0)) / lh + v[b, None] * (j.reshape(1, -1) + lo) / lw
+        a = turns * (-2.0 * math.pi)
+        flat = rows.reshape(N * ci, -1)
+        want[b] = ((flat @ a.cos().T.contiguous()) ** 2 + (flat @ a.sin().T.contiguous()) ** 2).sum(0)
+    want *= torch.where((v == 0) | (2 * v == lw), 1.0, 2.0)
+    err = float((got - want).norm() / want.norm())
+    say(f"[energies] {N * ci} planes of {sp}: {err}")
+    assert err <= 1.2e-8, err
+
+
 def test_tables_are_held_once(torch):
     """A series layer's transforms keep one table for the samples it takes and
     one for the samples it gives, whatever their place on the grid."""
