@@ -46,6 +46,8 @@ def main():
     ap.add_argument("--match", default="", help="further substring (e.g. template arguments)")
     ap.add_argument("--regex", default="", help="or: a regular expression the kernel symbol must match "
                                                  "(several instantiations under one library name)")
+    ap.add_argument("--launches", type=int, default=0, help="launches under the library's name in the run, where some "
+                                                            "of little traffic are other symbols' (0: those matched)")
     ap.add_argument("--name", required=True, help="the library's name for the kernel")
     ap.add_argument("--source", required=True)
     ap.add_argument("--copy-mib", type=int, required=True)
@@ -69,11 +71,11 @@ def main():
     kf, kw = pick(f, a.kernel, a.match, a.regex), pick(w, a.kernel, a.match, a.regex)
     if not kf or not kw:
         raise SystemExit("kernel not found")
-    fetch = sum(kf) / len(kf) * 1024.0 * read_scale
-    write = sum(kw) / len(kw) * 1024.0 * write_scale
+    fetch = sum(kf) / (a.launches or len(kf)) * 1024.0 * read_scale
+    write = sum(kw) / (a.launches or len(kw)) * 1024.0 * write_scale
     out = {"kernel": a.name, "symbol": a.regex or (a.kernel + a.match), "workload": a.workload,
            "source": a.source, "source_sha256_16": source_hash(a.source),
-           "dispatches": len(kf), "copy_mib": a.copy_mib,
+           "dispatches": a.launches or len(kf), "copy_mib": a.copy_mib,
            "read_scale": read_scale, "write_scale": write_scale,
            "fetch_bytes_per_launch": fetch, "write_bytes_per_launch": write,
            "traffic_bytes_per_launch": fetch + write}

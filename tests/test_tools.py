@@ -172,6 +172,22 @@ def test_traffic_scaled_by_copy(tmp_path):
     assert e["traffic_bytes_per_launch"] == pytest.approx(2000 * 2048 + 600 * 1024)
 
 
+def test_traffic_averages_over_the_names_launches(tmp_path):
+    """Launches of the library's name under other symbols count in the average, with no traffic."""
+    rows = [{"Dispatch_Id": "1", "Kernel_Name": "elementwise_kernel", "Counter_Name": "FETCH_SIZE",
+             "Counter_Value": str(1024)},
+            {"Dispatch_Id": "2", "Kernel_Name": "k_bluestein1k<3, 8>", "Counter_Name": "FETCH_SIZE",
+             "Counter_Value": "600"},
+            {"Dispatch_Id": "3", "Kernel_Name": "k_pgemm<true, 1, 4>", "Counter_Name": "FETCH_SIZE",
+             "Counter_Value": "7"}]
+    path, out = tmp_path / "c.csv", tmp_path / "t.json"
+    write_csv(path, rows)
+    run_tool("traffic", "--fetch", path, "--write", path, "--kernel", "k_bluestein1k", "--launches", 2, "--name",
+             "spec_inv_1d", "--source", __file__, "--copy-mib", 1, "--workload", "w", "--out", out)
+    e = json.load(open(out))["spec_inv_1d @ w"]
+    assert e["dispatches"] == 2 and e["traffic_bytes_per_launch"] == pytest.approx(600 * 1024)
+
+
 def test_bench_refuses_more_than_one_gpu():
     out = subprocess.run([sys.executable, "bench.py", "--gpus", "2"], cwd=ROOT, capture_output=True, text=True,
                          timeout=300)
