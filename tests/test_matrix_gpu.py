@@ -391,6 +391,18 @@ def test_tables_are_held_once(torch):
     assert held <= 2 * one + (8 << 20)  # (tiles, the other tables, and memory given out in blocks of 2 MB)
 
 
+@pytest.mark.parametrize("n", [240, 256, 270])
+def test_small_tables_of_a_plan(torch, n):
+    """Tables that share allocations: four of up to 256 KB, more than one
+    allocation holds, and (270 samples) some past that size with small ones."""
+    layer = synth.Layer("tables", 1, 3, 2, 5, n, 1, 8, (0, 0), "blur")
+    x, w, dy = synth.random_inputs(layer, 4700 + n)
+    got = gpu_passes(torch, layer, 0.0, x, w, dy, fft=300)
+    errs = [rel(g, r) for g, r in zip(got[:3], oracle_passes(layer, 0.0, x, w, dy, 300))]
+    say(f"[tables] {n} samples: {errs}")
+    assert max(errs) <= FP32_TOL, errs
+
+
 @pytest.mark.parametrize("nd,sp,K", [(2, (28, 21), 5), (2, (32, 32), 3), (1, (270,), 8)])
 def test_first_calls_from_two_threads(torch, nd, sp, K):
     """A new plan's first calls, from two threads on streams and workspaces of
