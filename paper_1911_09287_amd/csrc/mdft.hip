@@ -393,42 +393,40 @@ struct MdftTable {
 
 // The root tables of the two products as MFMA operands [tile][k step][part]
 // [lane][8], in double precision before the split; one thread per (tile, step,
-// lane).  Forward: Ew, then C and S of the kept rows; inverse: C and S of the
+// lane, k of eight).  Forward: Ew, then C and S of the kept rows; inverse: C and S of the
 // output rows, then the weighted column roots.
 template <bool INV>
 __global__ __launch_bounds__(256) void k_mdft_table(unsigned short* __restrict__ out, MdftTable g) {
-  const int id = blockIdx.x * 256 + threadIdx.x, lane = id & 63, first = g.n1 * g.ka;
-  int ts = id >> 6;  // tile and step
+  const int id = blockIdx.x * 256 + threadIdx.x, e = id & 7, lane = id >> 3 & 63, first = g.n1 * g.ka;
+  int ts = id >> 9;  // tile and step
   if (ts >= first + g.n2 * g.kb) return;
-  out += (size_t)ts * 1536 + lane * 8;
+  out += (size_t)ts * 1536 + lane * 8 + e;
   const bool one = ts < first;
   if (!one) ts -= first;
-  const int steps = one ? g.ka : g.kb, row = (ts / steps) * 16 + (lane & 15), k0 = (ts % steps) * 32 + 8 * (lane >> 4);
+  const int steps = one ? g.ka : g.kb, row = (ts / steps) * 16 + (lane & 15);
+  const int k = (ts % steps) * 32 + 8 * (lane >> 4) + e;
   auto turn = [](int m, int L, bool sine) {  // cos or sin of 2 pi m / L
     double c, s;
     sincospi(2.0 * (m % L) / L, &s, &c);
     return sine ? s : c;
   };
-  for (int e = 0; e < 8; ++e) {
-    const int k = k0 + e;
-    double v = 0.0;
-    if (one == INV) {  // cosines and sines along the columns of the grid
-      const int half = (one ? g.n1 : g.n2) / 2 * 16;  // the sines' first row
-      const int r = row < half ? row : row - half, u = INV ? k : r, i = INV ? r : k;
-      if (u <= g.r_h && i < g.H) v = turn(u * (i + g.oi), g.Lh, row >= half);
-    } else if constexpr (!INV) {  // x[j] e^{-2 pi i w (j + oj) / Lw}
-      const int w = row >> 1;
-      if (w < g.V && k < g.W) v = (row & 1) ? -turn(w * (k + g.oj), g.Lw, true) : turn(w * (k + g.oj), g.Lw, false);
-    } else {  // h_w Re((zr + i zi) e^{+2 pi i w (j + cj) / Lw})
-      const int w = k >> 1;
-      const bool real = w == 0 || 2 * w == g.Lw;
-      if (row < g.W && w < g.V && !(real && (k & 1))) {
-        const double t = turn(w * (row + g.oj), g.Lw, k & 1);
-        v = g.scale * (real ? 1.0 : 2.0) * ((k & 1) ? -t : t);
-      }
+  double v = 0.0;
+  if (one == INV) {  // cosines and sines along the columns of the grid
+    const int half = (one ? g.n1 : g.n2) / 2 * 16;  // the sines' first row
+    const int r = row < half ? row : row - half, u = INV ? k : r, i = INV ? r : k;
+    if (u <= g.r_h && i < g.H) v = turn(u * (i + g.oi), g.Lh, row >= half);
+  } else if constexpr (!INV) {  // x[j] e^{-2 pi i w (j + oj) / Lw}
+    const int w = row >> 1;
+    if (w < g.V && k < g.W) v = (row & 1) ? -turn(w * (k + g.oj), g.Lw, true) : turn(w * (k + g.oj), g.Lw, false);
+  } else {  // h_w Re((zr + i zi) e^{+2 pi i w (j + cj) / Lw})
+    const int w = k >> 1;
+    const bool real = w == 0 || 2 * w == g.Lw;
+    if (row < g.W && w < g.V && !(real && (k & 1))) {
+      const double t = turn(w * (row + g.oj), g.Lw, k & 1);
+      v = g.scale * (real ? 1.0 : 2.0) * ((k & 1) ? -t : t);
     }
-    split3_store(v, out + e, 512);
   }
+  split3_store(v, out, 512);
 }
 
 template <bool INV>
@@ -438,7 +436,7 @@ bl_status_t mdft_table(const bl_conv_plan_s* p, const MdftTable& t, const float2
   return plan_table_on_device(
       p, key, (size_t)n * 384,
       [&](float2* d) {
-        hipLaunchKernelGGL((k_mdft_table<INV>), dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s,
+        hipLaunchKernelGGL((k_mdft_table<INV>), dim3((unsigned)(2 * n)), dim3(256), 0, s,
                            reinterpret_cast<unsigned short*>(d), t);
       },
       tab, s);
