@@ -322,7 +322,7 @@ def main():
     def graphs_for(Ls):
         if not args.graph:
             return None
-        for L in Ls:  # eager once: uploads the plans' device tables before capture
+        for L in Ls:  # eager once: makes the plans' device tables before capture
             L.step()
         torch.cuda.synchronize()
         return capture(torch, Ls)

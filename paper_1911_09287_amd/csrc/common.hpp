@@ -85,8 +85,8 @@ bl_status_t plan_table(const bl_conv_plan_s* p, const std::vector<long>& key,
 // The same for a table of n float2 that `fill` makes by a kernel on stream s.
 // Nothing is built on the host or copied, and a call waits once for all of its
 // tables: what a new plan's first pass takes with tables made by the host / by
-// kernels is 214 / 116 us on a grid of 59 x 59 points (one image, forward), 333 /
-// 187 on 32 x 25 and 187 / 110 for 3 -> 16 channels on 34 x 34 (training steps).
+// kernels is 200 / 97 us on a grid of 59 x 59 points (one image, forward), 296 /
+// 172 on 32 x 25 and 180 / 114 for 3 -> 16 channels on 34 x 34 (training steps).
 bl_status_t plan_table_on_device(const bl_conv_plan_s* p, const std::vector<long>& key, size_t n,
                                  const std::function<void(float2*)>& fill, const float2** out, hipStream_t s);
 // Held by a compute call: what its kernels make is waited for once, when it
